@@ -97,7 +97,7 @@ void free_layer(gsq::Layer* L) {
   }
   for (hipEvent_t e : L->event_pool) (void)hipEventDestroy(e);
   void* bufs[] = {L->W, L->H, L->L, L->M, L->V, L->S, L->MS, L->VS, L->R[0], L->R[1],
-                  L->G, L->partials, L->loss_part, L->loss_stage, L->loss_tickets, L->split_ws,
+                  L->G, L->partials, L->loss_part, L->loss_stage, L->loss_tickets,
                   L->flag, L->sb_d, L->sb_sc, L->codes,
                   L->J0};
   for (void* p : bufs)
@@ -253,14 +253,14 @@ gsq_status gsq_layer_init(const gsq_config* cfg, const void* W, int32_t w_dtype,
   L.w_bf16 = w_dtype == GSQ_DT_BF16 ? 1 : 0;
   const size_t relem = L.bf16 ? 2 : 4;
   const size_t npad = (size_t)(L.B * L.Opad * L.Ipad);
-  L.tiles_per_batch = gsq::contract_tiles_per_batch(L);
   L.loss_cols = (L.I + 255) / 256;
   {
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) == hipSuccess) {
       L.device = dev;
-      if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
-        gsq::plan_contract_split(L, ncu);
+      if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+          ncu > 0)
+        L.num_cu = ncu;
     }
     (void)hipGetLastError();
   }
@@ -278,7 +278,7 @@ gsq_status gsq_layer_init(const gsq_config* cfg, const void* W, int32_t w_dtype,
             alloc(&L.V, gsq::state_floats(L) * 4) &&
             alloc(&L.S, L.NG * 4) && alloc(&L.MS, L.NG * 4) && alloc(&L.VS, L.NG * 4) &&
             alloc(&L.R[0], npad * relem) && alloc(&L.R[1], npad * relem) &&
-            alloc(&L.G, npad * 4) && alloc(&L.partials, (size_t)(L.B * L.tiles_per_batch) * 8) &&
+            alloc(&L.G, npad * 4) && alloc(&L.partials, (size_t)(L.B * gsq::contract_partials_per_batch(L)) * 8) &&
             alloc(&L.loss_part, (size_t)(L.B * L.O * L.loss_cols) * 8) &&
             alloc(&L.loss_stage, (size_t)gsq::loss_stage_size(L) * 8) &&
             alloc(&L.loss_tickets, (size_t)L.B * sizeof(unsigned)) &&
@@ -286,7 +286,6 @@ gsq_status gsq_layer_init(const gsq_config* cfg, const void* W, int32_t w_dtype,
   if (ok && cfg->layout == GSQ_LAYOUT_SUPERBLOCK)
     ok = alloc(&L.sb_d, (L.N / 256) * 2) && alloc(&L.sb_sc, L.N / 16);
   if (ok && cfg->relaxation == GSQ_RELAX_SHIFT) ok = alloc(&L.J0, (size_t)L.N);
-  if (ok && L.split_parts > 1) ok = alloc(&L.split_ws, (size_t)gsq::contract_split_ws_floats(L) * 4);
   if (!ok) {
     free_layer(h);
     return fail(GSQ_ENOMEM, "device allocation failed for a %lld x %lld x %lld layer",

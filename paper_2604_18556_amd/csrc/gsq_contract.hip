@@ -20,14 +20,27 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int BM = kTileM, BN = kTileN, BK = 64;
-constexpr int A_STAGES = 3;                              // LDS ring of R's K slabs
-constexpr int B_STAGES = 2;                              // LDS ring of H's K slabs
-constexpr int ROW_BYTES = BK * 2;                        // one 64-wide bf16 row: a full cache line
-constexpr int SLAB_BYTES = BM * ROW_BYTES;               // 32 KB per operand slab
-constexpr int B_BASE = A_STAGES * SLAB_BYTES;            // H's ring after R's
-constexpr size_t LDS_BYTES = (size_t)(A_STAGES + B_STAGES) * SLAB_BYTES;   // 160 KB
-constexpr int LOADS_PER_OPERAND = SLAB_BYTES / 1024 / 4;   // 1 KB loads per wavefront per operand slab
+constexpr int ROW_BYTES = BK * 2;    // one 64-wide bf16 row: a full cache line
 constexpr int GROUP_M = 8;           // tile rows swept together for L2 reuse
+constexpr size_t LDS_BYTES = 160 * 1024;
+
+// A workgroup's piece of a 256 x 256 tile: TM x TN outputs, and slabs loaded `AHEAD` ahead of the
+// one in use.  LDS holds a ring of AHEAD + 1 slabs of R and AHEAD of H.
+template <int TM_, int TN_, int AHEAD_>
+struct Piece {
+  static constexpr int TM = TM_, TN = TN_, AHEAD = AHEAD_;
+  static constexpr int A_STAGES = AHEAD + 1, B_STAGES = AHEAD;
+  static constexpr int A_SLAB = TM * ROW_BYTES, B_SLAB = TN * ROW_BYTES;
+  static constexpr int B_BASE = A_STAGES * A_SLAB;
+  static constexpr int A_LOADS = TM / 32, B_LOADS = TN / 32;   // 1 KB loads per wavefront and slab
+  static constexpr int MI = TM / 64, NJ = TN / 64;             // 32 x 32 blocks per wavefront
+  static_assert(B_BASE + B_STAGES * B_SLAB <= (int)LDS_BYTES, "the ring fits the LDS");
+};
+// The whole tile uses all the LDS; the smaller pieces, whose slabs last less long, load further
+// ahead where there is room (the quarter's 3.5 slabs of time equal the whole tile's 1.5).
+using Whole = Piece<256, 256, 2>;
+using Half = Piece<256, 128, 2>;
+using Quarter = Piece<128, 128, 4>;
 
 // Sum over the workgroup into *out, through `red` (blockDim.x doubles of LDS, free to reuse).
 __device__ __forceinline__ void block_sum_to(double x, double* out, double* red) {
@@ -41,11 +54,12 @@ __device__ __forceinline__ void block_sum_to(double x, double* out, double* red)
   if (threadIdx.x == 0) *out = red[0];
 }
 
-// Position of block `bid` in the tile order.  Workgroups are handed to the 8 XCDs round-robin;
-// renumbering so each XCD owns a contiguous range of the nblk blocks keeps the R and H panels a
-// group of tiles shares in the same XCD's L2.
+// Position of block `bid` of nblk in the tile order.  Workgroups are handed to the 8 XCDs
+// round-robin; renumbering so each XCD owns a contiguous range of the blocks keeps the R and H
+// panels a group of tiles shares in the same XCD's L2.
 __device__ __forceinline__ int lin_of(int bid, int nblk) {
-  return (nblk & 7) == 0 ? (bid & 7) * (nblk >> 3) + (bid >> 3) : bid;
+  const int x = bid & 7, base = nblk >> 3, rem = nblk & 7;
+  return x * base + min(x, rem) + (bid >> 3);
 }
 
 // Tile at position `lin`: GROUP_M tile rows are swept together, column by column.
@@ -58,51 +72,98 @@ __device__ __forceinline__ void tile_at(int lin, int tiles_m, int tiles_n, int& 
   tn = r / gsz;
 }
 
-// Work of one launch.  The first `full` blocks compute whole tiles (positions 0 .. full - 1).
-// When the tiles do not fill a whole number of rounds of the GPU, the tiles of the last, partly
-// empty round (positions full ..) are split along K: block full + q computes part q % split of
-// tile full + q / split and writes its raw P to ws; k_contract_fixup adds the parts in order.
-struct Split {
-  int full;
-  int split;    // 1: no split
-  float* ws;    // (tiles - full) x split x 256 x 256 fp32
-};
-
-// Batches of layers (MoE experts): the tiles of each layer are grouped into blocks of bm x bn
-// tiles (bm tile rows, bn tile columns, bm bn <= 32), one block per XCD at a time, so that the
-// 32 CUs of an XCD work on one layer's 32 tiles together and its L2 holds bm R panels and bn H
+// Work of one launch: the tiles of every layer, of which the last round of the GPU may fill only
+// some CUs.  Those tiles are cut into `parts` pieces (1, 2 or 4), one workgroup each.
+//
+// Without blocks, positions run over all layers' tiles; blocks 0 .. full - 1 take whole tiles and
+// the rest one piece each.
+//
+// With blocks (batches of layers with many tiles, e.g. MoE experts): the tiles of each layer are
+// grouped into blocks of bm x bn tiles (bm bn <= 32), one block per XCD at a time, so that the 32
+// CUs of an XCD work on one layer's 32 tiles together and its L2 holds bm R panels and bn H
 // panels for them.  Block q goes to XCD q mod 8 (workgroup w runs on XCD w mod 8); the XCD's
-// workgroups take its blocks in turn, 32 per block.
-struct XcdBlocks {
-  int on;
+// workgroups take its blocks in turn, 32 per block.  `full` then counts blocks, and each block
+// of the last round is spread over `parts` XCDs.
+struct Plan {
+  int tiles_m, tiles_n;
+  int full, parts;
+  int blocks;       // over all layers; 0: none
   int bm, bn;       // block shape in tiles
   int nbr, nbc;     // blocks per layer: rows, columns
-  int nblocks;      // over all layers
+  int slabs;        // K slabs that hold data
 };
 
-// One 256 x 256 tile of G per workgroup; four wavefronts each own 128 x 128 as 4 x 4 MFMA
-// 32x32x16 tiles.  K slabs 64 wide (whole 128-byte lines of R and H) move by direct global->LDS
-// loads (16 bytes per lane, no staging registers) into a ring of three buffers for R and two for
-// H, the whole 160 KB of LDS.  R's third buffer lets its slab k + 2 be loaded during the first
-// half of slab k, H's during the second: the loads split evenly between the halves and R's get
-// one and a half slabs of time to land.  The steady-state loop has no branches, so the fragment
-// reads and slab loads are spread between the matrix-core instructions (scheduling groups)
-// instead of stalling them.
-//
+// The piece of this workgroup: layer b, tile (tm, tn), piece `part` of `parts`.  False: none
+// (whole group).
+__device__ __forceinline__ bool pick_piece(const Plan& pl, int& b, int& tm, int& tn, int& part,
+                                           int& parts) {
+  parts = 1;
+  part = 0;
+  if (pl.blocks) {
+    const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
+    int q = (k >> 5) * 8 + x, j = k & 31;
+    const int per_block = pl.bm * pl.bn;
+    if (j >= per_block) return false;
+    if (q >= pl.full) {
+      parts = pl.parts;
+      const int s = q - pl.full;
+      q = pl.full + s / parts;
+      j += (s % parts) * per_block;   // piece j of the block's parts bm bn
+      part = j % parts;
+      j /= parts;
+    }
+    if (q >= pl.blocks) return false;
+    const int per_layer = pl.nbr * pl.nbc;
+    b = q / per_layer;
+    const int r = q - b * per_layer;
+    tm = (r / pl.nbc) * pl.bm + j % pl.bm;
+    tn = (r % pl.nbc) * pl.bn + j / pl.bm;
+    return tm < pl.tiles_m && tn < pl.tiles_n;
+  }
+  int lin;
+  if ((int)blockIdx.x < pl.full) {
+    lin = lin_of(blockIdx.x, pl.full);
+  } else {
+    parts = pl.parts;
+    const int q = lin_of(blockIdx.x - pl.full, (int)gridDim.x - pl.full);
+    lin = pl.full + q / parts;
+    part = q % parts;
+  }
+  const int tiles = pl.tiles_m * pl.tiles_n;
+  b = lin / tiles;
+  tile_at(lin - b * tiles, pl.tiles_m, pl.tiles_n, tm, tn);
+  return true;
+}
+
 // LDS layout of a slab: row r occupies 128 bytes as eight 16-byte chunks, chunk c stored at
 // position c ^ f(r), f(r) = (r ^ (r >> 3)) & 7.  The fragment reads (consecutive rows, one
 // chunk each) then fall on distinct banks for 8- and 16-lane access phases and for 32 or 64
 // banks.
 __device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
 
-// Global->LDS copy of one operand's slab rows 64 w .. 64 w + 63 (wave w): eight instructions of
-// eight rows, 16 bytes per lane.  `src` is wave-uniform (the slab's first column); off[j] is the
-// lane's element offset of instruction j, fixed for the whole K loop.
-__device__ __forceinline__ void load_slab(const uint16_t* src, const uint32_t (&off)[8],
+// Global->LDS copy of a wavefront's share of one operand slab: n instructions of eight rows, 16
+// bytes per lane.  `src` is wave-uniform (the slab's first column); off[j] is the lane's element
+// offset of instruction j, fixed for the whole K loop.
+__device__ __forceinline__ void load_rows(const uint16_t* src, uint8_t* lds) {
+  __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
+}
+
+template <int n>
+__device__ __forceinline__ void load_slab(const uint16_t* src, const uint32_t (&off)[n],
                                           uint8_t* lds_wave) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
-    __builtin_amdgcn_global_load_lds(src + off[j], lds_wave + j * 8 * ROW_BYTES, 16, 0, 0);
+  for (int j = 0; j < n; ++j) load_rows(src + off[j], lds_wave + j * 8 * ROW_BYTES);
+}
+
+// Lane offsets of those copies: row n 8 wave + 8 j + lane / 8, swizzled 16-byte chunk.
+template <int n>
+__device__ __forceinline__ void slab_offsets(uint32_t (&off)[n], int wave, int lane, int64_t Ipad) {
+#pragma unroll
+  for (int j = 0; j < n; ++j) {
+    const int row = wave * (n * 8) + j * 8 + (lane >> 3);
+    // < 256 Ipad + 64 <= 2^32 for the widest layer the library accepts (I <= 2^24)
+    off[j] = (uint32_t)row * (uint32_t)Ipad + (uint32_t)(((lane & 7) ^ swz(row)) * 8);
+  }
 }
 
 __device__ __forceinline__ bf16x8 read_frag(const uint8_t* lds, int row, int chunk) {
@@ -113,6 +174,7 @@ __device__ __forceinline__ bf16x8 read_frag(const uint8_t* lds, int row, int chu
 // in issue order), leaving LDS and scalar counters alone.
 template <int n>
 __device__ __forceinline__ void wait_vm() {
+  static_assert(n >= 0 && n < 64, "six bits");
   __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
 }
 
@@ -130,225 +192,220 @@ __device__ __forceinline__ void slab_barrier() {
 // scheduling-group masks
 constexpr int SG_MFMA = 0x008, SG_VMEM = 0x020, SG_DSR = 0x100;
 
-// Epilogue of a tile: the raw P of a split tile's K part into the workspace, else G = -2 P and,
-// on request, the tile's loss partial sum(R P).
-// 32 x 32 accumulator layout: lane l, register r -> row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-__device__ __forceinline__ void finish_tile(f32x16 (&acc)[4][4], const uint16_t* R, float* G,
-                                            double* partials, int64_t Opad, int64_t Ipad,
-                                            int tiles_m, int tiles_n, int want_loss,
-                                            const Split& sp, int64_t b, int tm, int tn, int part,
-                                            int lin, int wm, int wn, int lane, uint8_t* smem) {
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  if (part >= 0) {   // raw P of this K part, tile-local row-major
-    float* W_ = sp.ws + ((int64_t)(lin - sp.full) * sp.split + part) * (BM * BN);
+// Interleave one half-slab's M MFMAs with its R fragment reads and V slab loads: the reads first,
+// one per MFMA where there are enough MFMAs (the whole tile) and two where not, then one load per
+// MFMA, then the MFMAs left.
+template <int M, int R, int V>
+__device__ __forceinline__ void sched_half() {
+  constexpr int kReads = R + V <= M ? 1 : 2;
+  static_assert(R % kReads == 0 && R / kReads + V <= M, "every read and load has its MFMA");
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          W_[(wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * BN + wn * 128 + j * 32 +
-             (lane & 31)] = acc[i][j][r];
-    return;
+  for (int i = 0; i < R / kReads; ++i) {
+    __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(SG_DSR, kReads, 0);
   }
-  float* Gb = G + b * Opad * Ipad;
-  const uint16_t* Rb = R + b * Opad * Ipad;
-  double lsum = 0.0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = m0 + wm * 128 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int64_t col = n0 + wn * 128 + j * 32 + (lane & 31);
-        const float p = acc[i][j][r];
-        Gb[row * Ipad + col] = -2.f * p;
-        if (want_loss) lsum += (double)bf16_to_f32(Rb[row * Ipad + col]) * (double)p;
-      }
-  if (want_loss)
-    block_sum_to(lsum, partials + b * (int64_t)tiles_m * tiles_n + tm * tiles_n + tn,
-                 reinterpret_cast<double*>(smem));
+  for (int i = 0; i < V; ++i) {
+    __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(SG_VMEM, 1, 0);
+  }
+  if constexpr (M - R / kReads - V > 0)
+    __builtin_amdgcn_sched_group_barrier(SG_MFMA, M - R / kReads - V, 0);
 }
 
-// The tile of this workgroup: layer b, tile row tm, tile column tn, and for a split tile of the
-// last round its K part (part >= 0) as slabs kb .. kb + nk - 1.  False: no tile (whole group).
-__device__ __forceinline__ bool pick_tile(int tiles_m, int tiles_n, int64_t Ipad, const Split& sp,
-                                          const XcdBlocks& xb, int64_t& b, int& tm, int& tn,
-                                          int& part, int& kb, int& nk, int& lin) {
-  b = blockIdx.z;
-  nk = (int)(Ipad / BK);   // a multiple of 4 (Ipad is a multiple of 256)
-  lin = 0;
-  part = -1;
-  kb = 0;
-  if (xb.on) {
-    const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
-    const int q = (k >> 5) * 8 + x, j = k & 31;
-    if (q >= xb.nblocks || j >= xb.bm * xb.bn) return false;
-    const int per_layer = xb.nbr * xb.nbc;
-    b = q / per_layer;
-    const int r = q - (int)b * per_layer;
-    tm = (r / xb.nbc) * xb.bm + j % xb.bm;
-    tn = (r % xb.nbc) * xb.bn + j / xb.bm;
-    return tm < tiles_m && tn < tiles_n;
-  }
-  if ((int)blockIdx.x < sp.full) {
-    lin = lin_of(blockIdx.x, sp.full);
-  } else {   // a K part of a tile of the last round (XCD-contiguous numbering as well)
-    const int nq = (int)gridDim.x - sp.full;
-    const int q = lin_of(blockIdx.x - sp.full, nq);
-    lin = sp.full + q / sp.split;
-    part = q % sp.split;
-    nk /= sp.split;
-    kb = part * nk;
-  }
-  tile_at(lin, tiles_m, tiles_n, tm, tn);
-  return true;
-}
-
-__global__ __launch_bounds__(256, 1) void k_contract_bf16(const uint16_t* __restrict__ R,
-                                                          const uint16_t* __restrict__ H,
-                                                          float* __restrict__ G,
-                                                          double* __restrict__ partials,
-                                                          int64_t Opad, int64_t Ipad, int tiles_m,
-                                                          int tiles_n, int want_loss, Split sp,
-                                                          XcdBlocks xb) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  int64_t b;
-  int tm, tn, part, kb, nk, lin;
-  if (!pick_tile(tiles_m, tiles_n, Ipad, sp, xb, b, tm, tn, part, kb, nk, lin)) return;
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  const uint16_t* A = R + b * Opad * Ipad + m0 * Ipad + (int64_t)kb * BK;
-  const uint16_t* Bt = H + b * Ipad * Ipad + n0 * Ipad + (int64_t)kb * BK;
+// One piece of G per workgroup; four wavefronts each own a quarter of it (128 x 128 of a whole
+// tile) as MFMA 32x32x16 blocks.  K slabs 64 wide (whole 128-byte lines of R and H) move by direct
+// global->LDS loads (16 bytes per lane, no staging registers) into the two rings.  R's extra
+// buffer lets its slab k + AHEAD be loaded during the first half of slab k, H's during the second:
+// the loads split evenly between the halves.  The steady-state loop has no branches, so the
+// fragment reads and slab loads are spread between the matrix-core instructions (scheduling
+// groups) instead of stalling them.
+template <class P>
+__device__ __forceinline__ void contract_piece(const uint16_t* A, const uint16_t* Bt, float* Gp,
+                                               const uint16_t* Rp, double* partial, int64_t Ipad,
+                                               int nk, int want_loss, uint8_t* smem) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  f32x16 acc[4][4];
+  f32x16 acc[P::MI][P::NJ];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < P::MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < P::NJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  // lane offsets of the slab copies: row 64 wave + 8 j + lane / 8, swizzled 16-byte chunk
-  uint32_t off[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int row = wave * 64 + j * 8 + (lane >> 3);
-    // < 256 Ipad + 64 <= 2^32 for the widest layer the library accepts (I <= 2^24)
-    off[j] = (uint32_t)row * (uint32_t)Ipad + (uint32_t)(((lane & 7) ^ swz(row)) * 8);
-  }
-#define GSQ_ISSUE_A(K) \
-  load_slab(A + (int64_t)(K) * BK, off, smem + ((K) % A_STAGES) * SLAB_BYTES + wave * 64 * ROW_BYTES)
+  uint32_t offa[P::A_LOADS], offb[P::B_LOADS];
+  slab_offsets(offa, wave, lane, Ipad);
+  slab_offsets(offb, wave, lane, Ipad);   // the same registers where the counts agree
+#define GSQ_ISSUE_A(K)                                                                   \
+  load_slab(A + (int64_t)(K) * BK, offa,                                                 \
+            smem + ((K) % P::A_STAGES) * P::A_SLAB + wave * (P::TM / 4) * ROW_BYTES)
 #define GSQ_ISSUE_B(K)                                                                   \
-  load_slab(Bt + (int64_t)(K) * BK, off,                                                 \
-            smem + B_BASE + ((K) % B_STAGES) * SLAB_BYTES + wave * 64 * ROW_BYTES)
-  const int frow_a = wm * 128 + (lane & 31), frow_b = wn * 128 + (lane & 31);
+  load_slab(Bt + (int64_t)(K) * BK, offb,                                                \
+            smem + P::B_BASE + ((K) % P::B_STAGES) * P::B_SLAB + wave * (P::TN / 4) * ROW_BYTES)
+  const int frow_a = wm * (P::TM / 2) + (lane & 31), frow_b = wn * (P::TN / 2) + (lane & 31);
   const int fchunk = lane >> 5;
 
 // fragments of sub-steps 2 HALF and 2 HALF + 1 of slab K into register set S
 #define GSQ_READ(S, K, HALF)                                                             \
   do {                                                                                   \
-    const uint8_t* As_ = smem + ((K) % A_STAGES) * SLAB_BYTES;                           \
-    const uint8_t* Bs_ = smem + B_BASE + ((K) % B_STAGES) * SLAB_BYTES;                  \
-    _Pragma("unroll") for (int h = 0; h < 2; ++h)                                        \
-      _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                    \
-        const int c_ = (2 * (HALF) + h) * 2 + fchunk;                                    \
+    const uint8_t* As_ = smem + ((K) % P::A_STAGES) * P::A_SLAB;                         \
+    const uint8_t* Bs_ = smem + P::B_BASE + ((K) % P::B_STAGES) * P::B_SLAB;             \
+    _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                      \
+      const int c_ = (2 * (HALF) + h) * 2 + fchunk;                                      \
+      _Pragma("unroll") for (int i = 0; i < P::MI; ++i) {                                \
         S##a[h][i] = read_frag(As_, frow_a + i * 32, c_);                                \
-        S##b[h][i] = read_frag(Bs_, frow_b + i * 32, c_);                                \
+        if (i < P::NJ) S##b[h][i] = read_frag(Bs_, frow_b + i * 32, c_);                 \
       }                                                                                  \
+    }                                                                                    \
   } while (0)
 #define GSQ_MFMA(S)                                                                      \
   _Pragma("unroll") for (int h = 0; h < 2; ++h)                                          \
-    _Pragma("unroll") for (int i = 0; i < 4; ++i)                                        \
-      _Pragma("unroll") for (int j = 0; j < 4; ++j)                                      \
+    _Pragma("unroll") for (int i = 0; i < P::MI; ++i)                                    \
+      _Pragma("unroll") for (int j = 0; j < P::NJ; ++j)                                  \
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(S##a[h][i], S##b[h][j], acc[i][j], 0, 0, 0)
-// interleave: 16 x (one MFMA, one LDS read), then 8 x (one MFMA, one global->LDS load) and 8
-// MFMAs
-#define GSQ_SCHED_LOADS_READS()                                                          \
-  _Pragma("unroll") for (int i_ = 0; i_ < 16; ++i_) {                                    \
-    __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);                                 \
-    __builtin_amdgcn_sched_group_barrier(SG_DSR, 1, 0);                                  \
-  }                                                                                      \
-  _Pragma("unroll") for (int i_ = 0; i_ < 8; ++i_) {                                     \
-    __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);                                 \
-    __builtin_amdgcn_sched_group_barrier(SG_VMEM, 1, 0);                                 \
-  }                                                                                      \
-  __builtin_amdgcn_sched_group_barrier(SG_MFMA, 8, 0)
+  constexpr int kMfma = 2 * P::MI * P::NJ, kReads = 2 * (P::MI + P::NJ);
+  static_assert(P::MI >= P::NJ, "the fragment reads walk R's blocks");
 
   // p: first half (sub-steps 0, 1) of the current slab; q: second half (sub-steps 2, 3)
-  bf16x8 pa[2][4], pb[2][4], qa[2][4], qb[2][4];
-  GSQ_ISSUE_A(0);
-  GSQ_ISSUE_B(0);
-  GSQ_ISSUE_A(1);
-  GSQ_ISSUE_B(1);
-  wait_vm<2 * LOADS_PER_OPERAND>();
+  bf16x8 pa[2][P::MI], pb[2][P::NJ], qa[2][P::MI], qb[2][P::NJ];
+#pragma unroll
+  for (int k = 0; k < P::AHEAD; ++k) {
+    GSQ_ISSUE_A(k);
+    GSQ_ISSUE_B(k);
+  }
+  constexpr int kSlabLoads = P::A_LOADS + P::B_LOADS;
+  wait_vm<(P::AHEAD - 1) * kSlabLoads>();
   slab_barrier();
   GSQ_READ(p, 0, 0);
-  // steady state: R's slab kt + 2 is loaded during the first half of slab kt (its buffer last
+  // steady state: R's slab kt + AHEAD is loaded during the first half of slab kt (its buffer last
   // held slab kt - 1), H's during the second half (its buffer held slab kt, read by then)
-  for (int kt = 0; kt < nk - 2; ++kt) {
+  for (int kt = 0; kt < nk - P::AHEAD; ++kt) {
     GSQ_READ(q, kt, 1);
-    GSQ_ISSUE_A(kt + 2);
+    GSQ_ISSUE_A(kt + P::AHEAD);
     GSQ_MFMA(p);
-    GSQ_SCHED_LOADS_READS();
+    sched_half<kMfma, kReads, P::A_LOADS>();
     __builtin_amdgcn_sched_barrier(0);   // every MFMA of this half is issued before the wait
-    // slab kt+1 has landed (only R's slab kt+2 may be in flight), and every wavefront has read
-    // slab kt
-    wait_vm<LOADS_PER_OPERAND>();
+    // slab kt + 1 has landed (later ones, of kt + AHEAD only R's, may be in flight), and every
+    // wavefront has read slab kt
+    wait_vm<(P::AHEAD - 2) * kSlabLoads + P::A_LOADS>();
     slab_barrier();
     GSQ_READ(p, kt + 1, 0);
-    GSQ_ISSUE_B(kt + 2);
+    GSQ_ISSUE_B(kt + P::AHEAD);
     GSQ_MFMA(q);
-    GSQ_SCHED_LOADS_READS();
+    sched_half<kMfma, kReads, P::B_LOADS>();
     __builtin_amdgcn_sched_barrier(0);
   }
-  // the last two slabs: nothing more to load
-  GSQ_READ(q, nk - 2, 1);
-  GSQ_MFMA(p);
-  wait_vm<0>();
-  slab_barrier();
-  GSQ_READ(p, nk - 1, 0);
-  GSQ_MFMA(q);
+  // the last slabs: nothing more to load
+  for (int kt = nk - P::AHEAD; kt < nk - 1; ++kt) {
+    GSQ_READ(q, kt, 1);
+    GSQ_MFMA(p);
+    wait_vm<0>();
+    slab_barrier();
+    GSQ_READ(p, kt + 1, 0);
+    GSQ_MFMA(q);
+  }
   GSQ_READ(q, nk - 1, 1);
   GSQ_MFMA(p);
   GSQ_MFMA(q);
-#undef GSQ_SCHED_LOADS_READS
 #undef GSQ_MFMA
 #undef GSQ_READ
 #undef GSQ_ISSUE_A
 #undef GSQ_ISSUE_B
 
-  finish_tile(acc, R, G, partials, Opad, Ipad, tiles_m, tiles_n, want_loss, sp, b, tm, tn, part, lin,
-              wm, wn, lane, smem);
+  // G = -2 P and, on request, the piece's loss partial sum(R P).
+  // 32 x 32 accumulator layout: lane l, register r -> row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+  double lsum = 0.0;
+#pragma unroll
+  for (int i = 0; i < P::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < P::NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t row = wm * (P::TM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int64_t col = wn * (P::TN / 2) + j * 32 + (lane & 31);
+        const float p = acc[i][j][r];
+        Gp[row * Ipad + col] = -2.f * p;
+        if (want_loss) lsum += (double)bf16_to_f32(Rp[row * Ipad + col]) * (double)p;
+      }
+  if (want_loss) block_sum_to(lsum, partial, reinterpret_cast<double*>(smem));
 }
 
-// G = -2 (P_0 + ... + P_{split-1}) for the split tiles of the last round, parts added in order.
-// Block (q, y) covers rows y * FIX_ROWS .. of split tile q, so the fixup spreads over enough
-// workgroups to stream at the HBM rate.
-constexpr int FIX_ROWS = 32;
+// Loss partials: four per tile, of which a whole tile writes the first and clears the others, and
+// a piece writes its own (a half two, the second cleared).
+constexpr int TILE_PARTIALS = 4;
 
-__global__ __launch_bounds__(256) void k_contract_fixup(const float* __restrict__ ws,
-                                                        float* __restrict__ G, int64_t Ipad,
-                                                        int tiles_m, int tiles_n, Split sp) {
-  const int q = blockIdx.x;
-  int tm, tn;
-  tile_at(sp.full + q, tiles_m, tiles_n, tm, tn);
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  const float* src = ws + (int64_t)q * sp.split * (BM * BN);
-  const int lo = blockIdx.y * FIX_ROWS * BN, hi = lo + FIX_ROWS * BN;
-  for (int e = lo + threadIdx.x * 4; e < hi; e += 256 * 4) {
-    float4 acc = *reinterpret_cast<const float4*>(src + e);
-    for (int p = 1; p < sp.split; ++p) {
-      const float4 v = *reinterpret_cast<const float4*>(src + (int64_t)p * (BM * BN) + e);
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-    }
-    const int lr = e / BN, lc = e % BN;
-    *reinterpret_cast<float4*>(G + (m0 + lr) * Ipad + n0 + lc) =
-        make_float4(-2.f * acc.x, -2.f * acc.y, -2.f * acc.z, -2.f * acc.w);
+__global__ __launch_bounds__(256, 1) void k_contract_bf16(const uint16_t* __restrict__ R,
+                                                          const uint16_t* __restrict__ H,
+                                                          float* __restrict__ G,
+                                                          double* __restrict__ partials,
+                                                          int64_t Opad, int64_t Ipad, int O, int I,
+                                                          int want_loss, Plan pl) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  int b, tm, tn, part, parts;
+  if (!pick_piece(pl, b, tm, tn, part, parts)) return;
+  const int m0 = tm * BM + (parts == 4 ? (part >> 1) * Quarter::TM : 0);
+  const int n0 = tn * BN + (parts == 4 ? (part & 1) : parts == 2 ? part : 0) * Half::TN;
+  double* partial = partials + ((int64_t)b * pl.tiles_m * pl.tiles_n + tm * pl.tiles_n + tn) * TILE_PARTIALS + part;
+  if (want_loss && threadIdx.x == 0)
+    for (int k = part + parts; k < TILE_PARTIALS; k += parts) partial[k - part] = 0.0;
+  if (m0 >= O || n0 >= I) {   // a piece of padding only
+    if (want_loss && threadIdx.x == 0) *partial = 0.0;
+    return;
   }
+  const int64_t at = b * Opad * Ipad + (int64_t)m0 * Ipad;
+  const uint16_t* A = R + at;
+  const uint16_t* Bt = H + b * Ipad * Ipad + (int64_t)n0 * Ipad;
+  float* Gp = G + at + n0;
+  if (parts == 1)
+    contract_piece<Whole>(A, Bt, Gp, A + n0, partial, Ipad, pl.slabs, want_loss, smem);
+  else if (parts == 2)
+    contract_piece<Half>(A, Bt, Gp, A + n0, partial, Ipad, pl.slabs, want_loss, smem);
+  else
+    contract_piece<Quarter>(A, Bt, Gp, A + n0, partial, Ipad, pl.slabs, want_loss, smem);
+}
+
+// The plan of a layer's contraction on a GPU of num_cu compute units.  Tiles beyond a whole number
+// of rounds are cut where their pieces still fit one round: a piece per CU then takes about a half
+// or a third of a whole tile's time, against whole tiles on half the CUs or fewer.
+//   1024 x 4096 (64 tiles, as 256 quarters)              88 -> 44 us
+//   14336 x 4096 (3.5 rounds, the half as 256 halves)   448 -> 410 us
+//   4096 x 14336 (3.5 rounds)                          1376 us, the same as with the K range of
+//     the last tiles split over workgroups, which took a workspace and a second launch
+// A quarter's K loop is bound by its loads: 32 KB per slab and CU at 64 B per clock take as long
+// as its MFMAs.
+//
+// Blocks pay where a layer's block fills an XCD's 32 CUs about, and there are enough for each
+// XCD; else the tiles of all layers are numbered through.
+Plan make_plan(const Layer& L) {
+  Plan pl{};
+  pl.tiles_m = (int)(L.Opad / BM);
+  pl.tiles_n = (int)(L.Ipad / BN);
+  pl.slabs = (int)std::max<int64_t>((L.I + BK - 1) / BK, Quarter::AHEAD);   // Ipad holds 4 or more
+  pl.bm = std::min(pl.tiles_m, 8);
+  pl.bn = std::min(pl.tiles_n, 32 / pl.bm);
+  pl.nbr = (pl.tiles_m + pl.bm - 1) / pl.bm;
+  pl.nbc = (pl.tiles_n + pl.bn - 1) / pl.bn;
+  const bool blocks = L.B > 1 && pl.bm * pl.bn >= 24 && L.B * pl.nbr * pl.nbc >= 8;
+  const int64_t units = blocks ? L.B * pl.nbr * pl.nbc : L.B * pl.tiles_m * pl.tiles_n;
+  const int64_t round = blocks ? 8 : L.num_cu;
+  const int64_t rest = units % round;
+  pl.parts = rest == 0 ? 1 : rest * 4 <= round ? 4 : rest * 2 <= round ? 2 : 1;
+  pl.full = (int)(pl.parts == 1 ? units : units - rest);
+  pl.blocks = blocks ? (int)units : 0;
+  return pl;
+}
+
+// Workgroups of a plan.
+unsigned plan_grid(const Layer& L, const Plan& pl) {
+  if (pl.blocks) {
+    const int64_t slots = pl.full + (int64_t)(pl.blocks - pl.full) * pl.parts;
+    return (unsigned)(8 * 32 * ((slots + 7) / 8));
+  }
+  const int64_t units = L.B * pl.tiles_m * pl.tiles_n;
+  return (unsigned)(pl.full + (units - pl.full) * pl.parts);
 }
 
 // FP32 precision: 64 x 64 tile per workgroup, 4 x 4 outputs per thread, fp64 accumulation.
@@ -470,38 +527,18 @@ hipError_t prepare_contract_kernel() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_BYTES);
 }
 
-int64_t contract_tiles_per_batch(const Layer& L) {
-  return L.bf16 ? (L.Opad / BM) * (L.Ipad / BN) : (L.Opad / TM) * (L.Ipad / TN);
+int64_t contract_partials_per_batch(const Layer& L) {
+  return L.bf16 ? (L.Opad / BM) * (L.Ipad / BN) * TILE_PARTIALS : (L.Opad / TM) * (L.Ipad / TN);
 }
 
 hipError_t launch_contract(const Layer& L, const void* R, bool want_loss, int slot, hipStream_t s) {
   float* G = L.G + (int64_t)slot * L.B * L.Opad * L.Ipad;
   double* partials = L.partials;
   if (L.bf16) {
-    const int tiles_m = (int)(L.Opad / BM), tiles_n = (int)(L.Ipad / BN);
-    const int tiles = tiles_m * tiles_n;
-    Split sp{tiles, 1, nullptr};
-    if (L.split_parts > 1 && !want_loss) sp = Split{L.split_full, L.split_parts, L.split_ws};
-    dim3 grid((unsigned)(sp.full + (tiles - sp.full) * sp.split), 1, (unsigned)L.B);
-    XcdBlocks xb{0, 0, 0, 0, 0, 0};
-    if (L.B > 1) {   // one layer's block of tiles per XCD at a time
-      xb.on = 1;
-      xb.bm = std::min(tiles_m, 8);
-      xb.bn = std::min(tiles_n, 32 / xb.bm);
-      xb.nbr = (tiles_m + xb.bm - 1) / xb.bm;
-      xb.nbc = (tiles_n + xb.bn - 1) / xb.bn;
-      xb.nblocks = (int)L.B * xb.nbr * xb.nbc;
-      grid = dim3((unsigned)(8 * 32 * ((xb.nblocks + 7) / 8)), 1, 1);
-    }
-    hipLaunchKernelGGL(k_contract_bf16, grid, dim3(256), LDS_BYTES, s,
+    const Plan pl = make_plan(L);
+    hipLaunchKernelGGL(k_contract_bf16, dim3(plan_grid(L, pl)), dim3(256), LDS_BYTES, s,
                        static_cast<const uint16_t*>(R), static_cast<const uint16_t*>(L.H), G,
-                       partials, L.Opad, L.Ipad, tiles_m, tiles_n, want_loss ? 1 : 0, sp, xb);
-    if (sp.split > 1) {
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(k_contract_fixup, dim3((unsigned)(tiles - sp.full), BM / FIX_ROWS), dim3(256), 0, s,
-                         sp.ws, G, L.Ipad, tiles_m, tiles_n, sp);
-    }
+                       partials, L.Opad, L.Ipad, (int)L.O, (int)L.I, want_loss ? 1 : 0, pl);
   } else {
     dim3 grid((unsigned)(L.Ipad / TN), (unsigned)(L.Opad / TM), (unsigned)L.B);
     hipLaunchKernelGGL(k_contract_f32, grid, dim3(256), 0, s, static_cast<const float*>(R),
@@ -511,31 +548,8 @@ hipError_t launch_contract(const Layer& L, const void* R, bool want_loss, int sl
   return hipGetLastError();
 }
 
-void plan_contract_split(Layer& L, int num_cu) {
-  L.split_full = 0;
-  L.split_parts = 1;
-  if (!L.bf16 || L.B != 1 || num_cu <= 0) return;
-  const int tiles = (int)((L.Opad / BM) * (L.Ipad / BN));
-  const int rest = tiles % num_cu;
-  if (tiles < num_cu || rest == 0 || rest > num_cu / 2) return;
-  const int nk = (int)(L.Ipad / BK);
-  if (nk < 128) return;   // short K loops: the partial-product traffic would cost more than it saves
-  int split = 1;
-  for (int s = 2; s <= 4; s *= 2)
-    if (rest * s <= num_cu && nk % s == 0 && nk / s >= 2) split = s;
-  if (split == 1) return;
-  L.split_full = tiles - rest;
-  L.split_parts = split;
-}
-
-int64_t contract_split_ws_floats(const Layer& L) {
-  if (L.split_parts <= 1) return 0;
-  const int tiles = (int)((L.Opad / BM) * (L.Ipad / BN));
-  return (int64_t)(tiles - L.split_full) * L.split_parts * BM * BN;
-}
-
 int64_t loss_stage_size(const Layer& L) {
-  const int64_t most = std::max<int64_t>(L.O * L.loss_cols, contract_tiles_per_batch(L));
+  const int64_t most = std::max<int64_t>(L.O * L.loss_cols, contract_partials_per_batch(L));
   return L.B * ((most + kChunk - 1) / kChunk);
 }
 
@@ -553,7 +567,7 @@ hipError_t launch_reduce_loss(const Layer& L, float* loss_out, bool from_rows, d
 
 hipError_t launch_reduce_loss(const Layer& L, const double* part, double* stage, unsigned* tickets,
                               float* loss_out, bool from_rows, double scale, hipStream_t s) {
-  const int64_t per_batch = from_rows ? L.O * L.loss_cols : contract_tiles_per_batch(L);
+  const int64_t per_batch = from_rows ? L.O * L.loss_cols : contract_partials_per_batch(L);
   const int nchunks = (int)((per_batch + kChunk - 1) / kChunk);
   hipLaunchKernelGGL(k_reduce_loss, dim3((unsigned)nchunks, (unsigned)L.B), dim3(256), 0, s, part,
                      per_batch, nchunks, stage, tickets, scale, loss_out, L.flag);

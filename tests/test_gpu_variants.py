@@ -51,3 +51,49 @@ def test_state_copies(dev, K, O, I, gs, shift):
     codes = torch.empty(1, O, I, dtype=torch.uint8, device=dev)
     layer.harden(codes=codes)
     np.testing.assert_array_equal(codes.cpu().numpy(), want["logits"].argmax(-1))
+
+
+# ------------------------------------------------------------------ contraction
+# (batch, O, I): every way the work is cut.  Tiles are 256 x 256; a last round of at most a
+# quarter (half) of the 256 CUs is cut into quarters (halves).
+@pytest.mark.parametrize("B_,O,I", [
+    (1, 1, 16), (1, 129, 272), (1, 384, 640),       # quarters; 4 slabs and the shortest K loops
+    (1, 300, 8256), (5, 300, 528),                  # quarters, ragged, over a batch
+    (1, 1900, 3904), (17, 500, 512),                # halves only
+    (1, 2048, 4352), (1, 4080, 4096),               # whole tiles only, below and at a round
+    (1, 1000, 16400), (1, 5300, 4112),              # a whole round, then quarters; then halves
+    (8, 2048, 1024), (9, 1800, 1008), (12, 2048, 1008),   # blocks: whole; a quartered; halved
+    (10, 4200, 1040),                               # blocks that the last row of tiles does not fill
+])
+def test_contraction_cuts(dev, B_, O, I):
+    """G = -2 R H of the library's own R against a float64 product of the same bf16 operands, and
+    the hard loss against sum(R (R H)) of the hard residual, over the cuts of the work.
+
+    Sums of I fp32 products in any order: an error of about 2^-24 sqrt(I) of the result's norm."""
+    gen = torch.Generator(device=dev).manual_seed(O + I)
+    W = (torch.randn(B_, O, I, generator=gen, device=dev) * 0.02).to(torch.bfloat16)
+    X = torch.randn(B_, 512, I, generator=gen, device=dev)
+    H = torch.stack([x.t() @ x for x in X])
+    c = torch.tensor([-1.5, -0.5, 0.5, 1.5], device=dev, dtype=torch.float64)
+    cfg = B.LayerConfig(O, I, tuple(c.tolist()), 16, batch=B_, seed=4)
+    layer = B.Layer(cfg, W, H)
+    layer.step(B.StepParams(tau=0.7))
+    R = torch.empty(B_, O, I, device=dev, dtype=torch.bfloat16)
+    G = torch.empty(B_, O, I, device=dev)
+    layer.intermediates(R, G)
+    codes = torch.empty(B_, O, I, dtype=torch.uint8, device=dev)
+    scales = torch.empty(B_, O, I // 16, device=dev)
+    hard = torch.zeros(B_, device=dev)
+    layer.harden(codes=codes, scales=scales, hard_loss=hard)
+    tol = 4 * 2.0 ** -24 * I ** 0.5
+    for b in range(B_):
+        Hb = ((H[b] + H[b].t()) * 0.5).to(torch.bfloat16).double()
+        want = -2.0 * (R[b].double() @ Hb)
+        err = (G[b].double() - want).norm() / want.norm()
+        assert err <= tol, f"layer {b}: {err:.2e} > {tol:.2e}"
+        worst = (G[b].double() - want).abs().max() / want.abs().max()
+        assert worst <= 10 * tol, f"layer {b}: an element off by {worst:.2e}"
+        q = c[codes[b].long()].float() * scales[b].repeat_interleave(16, 1)
+        Rh = (W[b].float() - q).to(torch.bfloat16).double()
+        loss = (Rh * (Rh @ Hb)).sum()
+        assert abs(hard[b].double() - loss) <= max(tol, 2e-6) * loss, (b, hard[b].item(), loss.item())
