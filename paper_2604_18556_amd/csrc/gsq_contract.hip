@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256, 1) void k_contract_bf16(const uint16_t* __rest
 // The plan of a layer's contraction on a GPU of num_cu compute units.  Tiles beyond a whole number
 // of rounds are cut where their pieces still fit one round: a piece per CU then takes about a half
 // or a third of a whole tile's time, against whole tiles on half the CUs or fewer.
-//   1024 x 4096 (64 tiles, as 256 quarters)              88 -> 44 us
+//   1024 x 4096 (64 tiles, as 256 quarters)              88 -> 45 us
 //   14336 x 4096 (3.5 rounds, the half as 256 halves)   448 -> 410 us
 //   4096 x 14336 (3.5 rounds)                          1376 us, the same as with the K range of
 //     the last tiles split over workgroups, which took a workspace and a second launch
@@ -408,62 +408,110 @@ unsigned plan_grid(const Layer& L, const Plan& pl) {
   return (unsigned)(pl.full + (units - pl.full) * pl.parts);
 }
 
-// FP32 precision: 64 x 64 tile per workgroup, 4 x 4 outputs per thread, fp64 accumulation.
-constexpr int TM = 64, TN = 64, TK = 16;
+// FP32 precision: products of fp32 values, exact in fp64 and summed in fp64, on the fp64 matrix
+// cores (v_mfma 16x16x4 f64; their rate is the vector units', 78.6 TFLOP/s, but a fragment is
+// read and converted once per 16 x 16 block instead of once per product).  A tile of 32 W x 32 W
+// per workgroup, four wavefronts of 16 W x 16 W each; K slabs 32 wide go through registers into
+// two LDS buffers while the other is used.  Rows of 36 floats keep the fragment reads (16 rows,
+// 4 x 4 columns, 16 bytes per lane) on distinct banks.  1024 x 2048: 293 us with vector fmas (29
+// TFLOP/s), 161 us here (53); 256 x 256: 24 -> 7.4 us.  The launch bound of two wavefronts per
+// SIMD keeps the accumulators out of the AGPRs, whose copies cost a tenth of the loop.
+//
+// MFMA lane l holds row (column) l % 16 and one of four k.  A lane reads four consecutive floats
+// at 4 (l / 16), one for each of four MFMAs: the same k on both sides, in another order than
+// memory's.  Result: lane l, register r -> row 4 r + l / 16, column l % 16.
+constexpr int SK = 32, SK_ROW = SK + 4;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_contract_f32(const float* __restrict__ R,
+template <int W>
+__global__ __launch_bounds__(256, 2) void k_contract_f32(const float* __restrict__ R,
                                                       const float* __restrict__ H,
                                                       float* __restrict__ G,
                                                       double* __restrict__ partials, int64_t Opad,
-                                                      int64_t Ipad, int want_loss) {
-  __shared__ float As[TK][TM + 1];
-  __shared__ float Bs[TK][TN + 1];
+                                                      int64_t Ipad, int slabs, int want_loss) {
+  constexpr int T = 32 * W;
+  __shared__ __align__(16) float As[2][T * SK_ROW], Bs[2][T * SK_ROW];
   const int64_t b = blockIdx.z;
-  const int64_t m0 = (int64_t)blockIdx.y * TM, n0 = (int64_t)blockIdx.x * TN;
+  const int64_t m0 = (int64_t)blockIdx.y * T, n0 = (int64_t)blockIdx.x * T;
   const float* A = R + b * Opad * Ipad + m0 * Ipad;
   const float* Bt = H + b * Ipad * Ipad + n0 * Ipad;
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  double acc[4][4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * 16 * W, wn = (wave & 1) * 16 * W;
+  const int lrow = tid >> 3, lcol = (tid & 7) * 4;   // this thread's part of 32 rows of a slab
+
+  f64x4 acc[W][W];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < W; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-  for (int64_t k0 = 0; k0 < Ipad; k0 += TK) {
+    for (int j = 0; j < W; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+
+  f32x4 ra[W], rb[W];
+#define GSQ_FETCH(KT)                                                                    \
+  _Pragma("unroll") for (int i = 0; i < W; ++i) {                                        \
+    const int64_t at_ = (lrow + 32 * i) * Ipad + (int64_t)(KT) * SK + lcol;              \
+    ra[i] = *reinterpret_cast<const f32x4*>(A + at_);                                    \
+    rb[i] = *reinterpret_cast<const f32x4*>(Bt + at_);                                   \
+  }
+#define GSQ_STAGE(BUF)                                                                   \
+  _Pragma("unroll") for (int i = 0; i < W; ++i) {                                        \
+    *reinterpret_cast<f32x4*>(&As[BUF][(lrow + 32 * i) * SK_ROW + lcol]) = ra[i];        \
+    *reinterpret_cast<f32x4*>(&Bs[BUF][(lrow + 32 * i) * SK_ROW + lcol]) = rb[i];        \
+  }
+  GSQ_FETCH(0);
+  GSQ_STAGE(0);
+  __syncthreads();
+  for (int kt = 0; kt < slabs; ++kt) {
+    const int cur = kt & 1;
+    GSQ_FETCH(min(kt + 1, slabs - 1));   // the last slab again at the end: no branch
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = tid + 256 * i, row = c >> 4, k = c & 15;
-      As[k][row] = A[row * Ipad + k0 + k];
-      Bs[k][row] = Bt[row * Ipad + k0 + k];
+    for (int h = 0; h < SK / 16; ++h) {
+      f32x4 a[W], c[W];
+#pragma unroll
+      for (int i = 0; i < W; ++i) {
+        const int at = (lane & 15) * SK_ROW + 16 * h + 4 * (lane >> 4);
+        a[i] = *reinterpret_cast<const f32x4*>(&As[cur][(wm + 16 * i) * SK_ROW + at]);
+        c[i] = *reinterpret_cast<const f32x4*>(&Bs[cur][(wn + 16 * i) * SK_ROW + at]);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+#pragma unroll
+          for (int j = 0; j < W; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[i][k], (double)c[j][k],
+                                                             acc[i][j], 0, 0, 0);
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < TK; ++k) {
-      double av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { av[i] = As[k][ty * 4 + i]; bv[i] = Bs[k][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
-    }
+    GSQ_STAGE(cur ^ 1);   // last read in the round before, whose barrier is past
     __syncthreads();
   }
+#undef GSQ_FETCH
+#undef GSQ_STAGE
   double lsum = 0.0;
   float* Gb = G + b * Opad * Ipad;
   const float* Rb = R + b * Opad * Ipad;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < W; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-      Gb[row * Ipad + col] = (float)(-2.0 * acc[i][j]);
-      if (want_loss) lsum += (double)Rb[row * Ipad + col] * acc[i][j];
-    }
-  if (want_loss)
-  {
+    for (int j = 0; j < W; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t row = m0 + wm + 16 * i + 4 * r + (lane >> 4);
+        const int64_t col = n0 + wn + 16 * j + (lane & 15);
+        Gb[row * Ipad + col] = (float)(-2.0 * acc[i][j][r]);
+        if (want_loss) lsum += (double)Rb[row * Ipad + col] * acc[i][j][r];
+      }
+  if (want_loss) {
     __shared__ double red[256];
     block_sum_to(lsum, partials + (b * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, red);
   }
+}
+
+// Tile of that kernel in units of 32: 64 x 64, or 32 x 32 where the larger tiles would not give
+// every CU one (256 x 256: 7.4 us with 32 x 32 tiles, 14.0 with 64 x 64).
+int f32_tile(const Layer& L) {
+  const int64_t tiles = L.B * ((L.O + 63) / 64) * ((L.I + 63) / 64);
+  return tiles >= L.num_cu ? 2 : 1;
 }
 
 // Loss of layer b = scale * the sum of its per_batch partials, in a fixed order, in one launch:
@@ -528,7 +576,9 @@ hipError_t prepare_contract_kernel() {
 }
 
 int64_t contract_partials_per_batch(const Layer& L) {
-  return L.bf16 ? (L.Opad / BM) * (L.Ipad / BN) * TILE_PARTIALS : (L.Opad / TM) * (L.Ipad / TN);
+  if (L.bf16) return (L.Opad / BM) * (L.Ipad / BN) * TILE_PARTIALS;
+  const int t = 32 * f32_tile(L);
+  return ((L.O + t - 1) / t) * ((L.I + t - 1) / t);
 }
 
 hipError_t launch_contract(const Layer& L, const void* R, bool want_loss, int slot, hipStream_t s) {
@@ -540,10 +590,16 @@ hipError_t launch_contract(const Layer& L, const void* R, bool want_loss, int sl
                        static_cast<const uint16_t*>(R), static_cast<const uint16_t*>(L.H), G,
                        partials, L.Opad, L.Ipad, (int)L.O, (int)L.I, want_loss ? 1 : 0, pl);
   } else {
-    dim3 grid((unsigned)(L.Ipad / TN), (unsigned)(L.Opad / TM), (unsigned)L.B);
-    hipLaunchKernelGGL(k_contract_f32, grid, dim3(256), 0, s, static_cast<const float*>(R),
-                       static_cast<const float*>(L.H), G, partials, L.Opad, L.Ipad,
-                       want_loss ? 1 : 0);
+    const int w = f32_tile(L), t = 32 * w, slabs = (int)((L.I + SK - 1) / SK);
+    const dim3 grid((unsigned)((L.I + t - 1) / t), (unsigned)((L.O + t - 1) / t), (unsigned)L.B);
+    const float* Rf = static_cast<const float*>(R);
+    const float* Hf = static_cast<const float*>(L.H);
+    if (w == 2)
+      hipLaunchKernelGGL(k_contract_f32<2>, grid, dim3(256), 0, s, Rf, Hf, G, partials, L.Opad,
+                         L.Ipad, slabs, want_loss ? 1 : 0);
+    else
+      hipLaunchKernelGGL(k_contract_f32<1>, grid, dim3(256), 0, s, Rf, Hf, G, partials, L.Opad,
+                         L.Ipad, slabs, want_loss ? 1 : 0);
   }
   return hipGetLastError();
 }

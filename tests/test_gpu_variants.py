@@ -97,3 +97,33 @@ def test_contraction_cuts(dev, B_, O, I):
         Rh = (W[b].float() - q).to(torch.bfloat16).double()
         loss = (Rh * (Rh @ Hb)).sum()
         assert abs(hard[b].double() - loss) <= max(tol, 2e-6) * loss, (b, hard[b].item(), loss.item())
+
+
+# (batch, O, I) of the FP32 precision: 32 x 32 and 64 x 64 tiles, K slabs of 32, ragged ends
+@pytest.mark.parametrize("B_,O,I", [(1, 1, 16), (1, 33, 48), (1, 256, 256), (3, 100, 208),
+                                    (1, 1000, 1040), (2, 520, 1024), (1, 65, 16384)])
+def test_contraction_fp32(dev, B_, O, I):
+    """G = -2 R H of fp32 operands with fp64 sums, rounded once to fp32, and the hard loss."""
+    gen = torch.Generator(device=dev).manual_seed(O + I)
+    W = torch.randn(B_, O, I, generator=gen, device=dev) * 0.02
+    X = torch.randn(B_, 64, I, generator=gen, device=dev)
+    H = torch.stack([x.t() @ x for x in X])
+    c = torch.tensor([-1.5, -0.5, 0.5, 1.5], device=dev)
+    cfg = B.LayerConfig(O, I, tuple(c.tolist()), 16, batch=B_, seed=4, precision=B.PREC_FP32)
+    layer = B.Layer(cfg, W, H)
+    layer.step(B.StepParams(tau=0.7))
+    R, G = torch.empty(B_, O, I, device=dev), torch.empty(B_, O, I, device=dev)
+    layer.intermediates(R, G)
+    codes = torch.empty(B_, O, I, dtype=torch.uint8, device=dev)
+    scales = torch.empty(B_, O, I // 16, device=dev)
+    hard = torch.zeros(B_, device=dev)
+    layer.harden(codes=codes, scales=scales, hard_loss=hard)
+    for b in range(B_):
+        Hb = ((H[b] + H[b].t()) * 0.5).double()
+        want = -2.0 * (R[b].double() @ Hb)
+        # one rounding to fp32 of a sum whose fp64 error is far below it (|G| is not tiny next to
+        # the terms: they are random)
+        assert (G[b].double() - want).abs().max() <= 2.0 ** -23 * want.abs().max()
+        Rh = (W[b] - scales[b].repeat_interleave(16, 1) * c[codes[b].long()]).double()
+        loss = (Rh * (Rh @ Hb)).sum()
+        assert abs(hard[b].double() - loss) <= 2e-6 * loss, (b, hard[b].item(), loss.item())
