@@ -608,65 +608,105 @@ __global__ __launch_bounds__(kBlock) void k_backward(
 }
 
 // ------------------------------------------------------------------ initialisation
-__global__ void k_symmetrize(const float* __restrict__ Hin, void* Hout, int64_t I, int64_t Ipad,
-                             int bf16) {
-  __shared__ float tile[32][33];
+// sym = (H + H^T) / 2 in the contraction's type and padding.  Bound by HBM: H read once, the result
+// written once.  A block takes the 64 x 64 tiles (i, j) and (j, i) together through LDS, which is
+// both halves of either tile's sum; rows of 65 floats keep the transposed reads on distinct banks.
+// 4 x 7168^2 to bf16: 600 us with each tile's two halves read by its own block, 241 us here.
+constexpr int kSymT = 64;
+
+template <bool kBf16>
+__global__ __launch_bounds__(kBlock) void k_symmetrize(const float* __restrict__ Hin, void* Hout,
+                                                       int64_t I, int64_t Ipad) {
+  if (blockIdx.x < blockIdx.y) return;
+  __shared__ float up[kSymT][kSymT + 1], low[kSymT][kSymT + 1];
   const int64_t b = blockIdx.z;
-  const int64_t i0 = (int64_t)blockIdx.y * 32, j0 = (int64_t)blockIdx.x * 32;
+  const int64_t i0 = (int64_t)blockIdx.y * kSymT, j0 = (int64_t)blockIdx.x * kSymT;
   const float* H = Hin + b * I * I;
-  for (int r = threadIdx.y; r < 32; r += 8) {
-    const int64_t j = j0 + r, i = i0 + threadIdx.x;
-    tile[r][threadIdx.x] = (j < I && i < I) ? H[j * I + i] : 0.f;
+  const int c = threadIdx.x & 63;
+  // every load in flight before the first use; past the edge the nearest element, not used
+  const int r0 = threadIdx.x >> 6;
+  const int64_t ju = min(j0 + c, I - 1), jl = min(i0 + c, I - 1);
+  constexpr int kRows = kSymT / (kBlock / 64);
+  float u[kRows], l[kRows];
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) {
+    const int r = r0 + k * (kBlock / 64);
+    u[k] = H[min(i0 + r, I - 1) * I + ju];
+    l[k] = H[min(j0 + r, I - 1) * I + jl];
+  }
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) {
+    const int r = r0 + k * (kBlock / 64);
+    up[r][c] = (i0 + r < I && j0 + c < I) ? u[k] : 0.f;
+    low[r][c] = (j0 + r < I && i0 + c < I) ? l[k] : 0.f;
   }
   __syncthreads();
-  for (int r = threadIdx.y; r < 32; r += 8) {
-    const int64_t i = i0 + r, j = j0 + threadIdx.x;
-    const float x = (i < I && j < I) ? H[i * I + j] : 0.f;
-    const float sym = (x + tile[threadIdx.x][r]) * 0.5f;
+  const int c2 = (threadIdx.x & 31) * 2;
+  const auto put = [&](int64_t i, int64_t j, float x, float y) {
     const int64_t o = b * Ipad * Ipad + i * Ipad + j;
-    if (bf16) static_cast<uint16_t*>(Hout)[o] = bf16_rne(sym);
-    else static_cast<float*>(Hout)[o] = sym;
+    if constexpr (kBf16)
+      *reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(Hout) + o) =
+          (uint32_t)bf16_rne(x) | ((uint32_t)bf16_rne(y) << 16);
+    else
+      *reinterpret_cast<float2*>(static_cast<float*>(Hout) + o) = make_float2(x, y);
+  };
+#pragma unroll 4
+  for (int r = threadIdx.x >> 5; r < kSymT; r += kBlock / 32) {
+    put(i0 + r, j0 + c2, (up[r][c2] + low[c2][r]) * 0.5f, (up[r][c2 + 1] + low[c2 + 1][r]) * 0.5f);
+    put(j0 + r, i0 + c2, (low[r][c2] + up[c2][r]) * 0.5f, (low[r][c2 + 1] + up[c2 + 1][r]) * 0.5f);
   }
 }
 
-__device__ __forceinline__ float load_w1(const void* W, int w_bf16, int64_t e) {
-  return w_bf16 ? bf16_to_f32(static_cast<const uint16_t*>(W)[e]) : static_cast<const float*>(W)[e];
+// Largest |W| of an aligned run of 4 n consecutive weights, four per lane over n lanes (a power of
+// two); NaNs are passed over, as by fmaxf.
+__device__ __forceinline__ float run_absmax(const float (&w)[4], int n) {
+  float m = fmaxf(fmaxf(fabsf(w[0]), fabsf(w[1])), fmaxf(fabsf(w[2]), fabsf(w[3])));
+  m = fmaxf(0.f, m);
+  for (int off = 1; off < n; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  return m;
 }
 
-// s = max|W_group| / max|c| (IEEE division), 1 for an all-zero group.
-__global__ void k_init_scales_group(const void* W, int w_bf16, float* S, int64_t ngroups, int gs,
-                                    float cmax) {
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < ngroups;
-       g += (int64_t)gridDim.x * blockDim.x) {
-    float amax = 0.f;
-    for (int i = 0; i < gs; ++i) amax = fmaxf(amax, fabsf(load_w1(W, w_bf16, g * gs + i)));
-    const float s = __fdiv_rn(amax, cmax);
-    S[g] = s == 0.f ? 1.f : s;
+// s = max|W_group| / max|c| (IEEE division), 1 for an all-zero group.  Four weights per lane, read
+// in order: a group lies inside a wavefront's 256.  14336 x 4096 in groups of 128: 823 us with one
+// thread per group, 58 us here.
+__global__ __launch_bounds__(kBlock) void k_init_scales_group(const void* W, int w_bf16, float* S,
+                                                              int64_t N, int gs, float cmax) {
+  for (int64_t e = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4;
+       e - 4 * (int)(threadIdx.x & 63) < N; e += (int64_t)gridDim.x * kBlock * 4) {
+    float w[4] = {0.f, 0.f, 0.f, 0.f};
+    if (e < N) load_w4(W, w_bf16, e, w);   // whole wavefronts stay for the shuffles
+    const float amax = run_absmax(w, gs / 4);
+    if (e < N && e % gs == 0) {
+      const float s = __fdiv_rn(amax, cmax);
+      S[e / gs] = s == 0.f ? 1.f : s;
+    }
   }
 }
 
 // 256-weight super-block: d = fp16(max_j s_j / 63), sc_j = clamp(rint(s_j / d), 0, 63),
-// effective scale d * sc_j per 16-weight sub-block.
-__global__ void k_init_scales_superblock(const void* W, int w_bf16, float* S, uint16_t* D,
-                                         uint8_t* SC, int64_t nblocks, float cmax) {
-  for (int64_t sb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; sb < nblocks;
-       sb += (int64_t)gridDim.x * blockDim.x) {
-    float raw[16];
-    float mx = 0.f;
-    for (int j = 0; j < 16; ++j) {
-      float amax = 0.f;
-      for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(load_w1(W, w_bf16, sb * 256 + j * 16 + i)));
-      raw[j] = __fdiv_rn(amax, cmax);
-      mx = fmaxf(mx, raw[j]);
-    }
+// effective scale d * sc_j per 16-weight sub-block.  One wavefront per super-block, four weights
+// per lane.  4 x 2048 x 7168: 482-783 us with one thread per super-block, 61 us here.
+__global__ __launch_bounds__(kBlock) void k_init_scales_superblock(const void* W, int w_bf16,
+                                                                   float* S, uint16_t* D,
+                                                                   uint8_t* SC, int64_t nblocks,
+                                                                   float cmax) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t sb = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); sb < nblocks;
+       sb += (int64_t)gridDim.x * (kBlock / 64)) {
+    float w[4];
+    load_w4(W, w_bf16, sb * 256 + lane * 4, w);
+    const float raw = __fdiv_rn(run_absmax(w, 4), cmax);
+    float mx = fmaxf(0.f, raw);
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
     const __half dh = __float2half_rn(__fdiv_rn(mx, 63.f));
     const float d = __half2float(dh);
-    D[sb] = __half_as_ushort(dh);
-    for (int j = 0; j < 16; ++j) {
-      const float q = d > 0.f ? __fdiv_rn(raw[j], d) : 0.f;
+    if (lane == 0) D[sb] = __half_as_ushort(dh);
+    if ((lane & 3) == 0) {
+      const float q = d > 0.f ? __fdiv_rn(raw, d) : 0.f;
       const float scq = fminf(fmaxf(rintf(q), 0.f), 63.f);
-      SC[sb * 16 + j] = (uint8_t)scq;
-      S[sb * 16 + j] = d * scq;
+      SC[sb * 16 + lane / 4] = (uint8_t)scq;
+      S[sb * 16 + lane / 4] = d * scq;
     }
   }
 }
@@ -674,9 +714,7 @@ __global__ void k_init_scales_superblock(const void* W, int w_bf16, float* S, ui
 struct InitConsts {
   float c[GSQ_MAX_LEVELS];
   double mids[GSQ_MAX_LEVELS];   // (c_k + c_{k+1}) / 2, exact in fp64
-  int K;                         // logits per coordinate
   int n_grid;
-  int relax;
   float alpha, sigma;
   int noise;
   uint64_t seed;
@@ -688,49 +726,71 @@ struct InitConsts {
 //   GRID: prior_k = -(c_k - c_q)^2 / 2, mean-subtracted (App. A);
 //   SHIFT: j0 = q and prior_k = -delta_k^2 / 2, mean-subtracted (App. A, b > 2);
 //   TERNARY: Eq. 3, prior = (q != 0 ? 1 : -1, sign of q) for the level c_q in {-1, 0, 1}.
-// fp64 arithmetic, fp32 storage.
-__global__ void k_init_logits(const void* W, int w_bf16, const float* S, float* L, uint8_t* J0,
-                              int64_t N, int gs, InitConsts ic) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < N;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const float w = load_w1(W, w_bf16, e);
-    const float s = S[e / gs];
-    const float u = s != 0.f ? __fdiv_rn(w, s) : 0.f;
-    int q = 0;
-    for (int k = 0; k + 1 < ic.n_grid; ++k) q += ((double)u > ic.mids[k]) ? 1 : 0;
-    double mu[8], mean = 0.0;
-    if (ic.relax == GSQ_RELAX_TERNARY) {
-      mu[0] = q != 1 ? 1.0 : -1.0;
-      mu[1] = (double)(q - 1);
-    } else {
-      double cq = 0.0;
-      for (int k = 0; k < ic.n_grid; ++k) if (k == q) cq = (double)ic.c[k];
-      for (int k = 0; k < ic.K; ++k) {
-        const double dlt = ic.relax == GSQ_RELAX_SHIFT ? (double)(k - 2) : (double)ic.c[k] - cq;
-        mu[k] = -0.5 * dlt * dlt;
-        mean += mu[k];
-      }
-      mean /= (double)ic.K;
-      if (ic.relax == GSQ_RELAX_SHIFT) J0[e] = (uint8_t)q;
-    }
-    float eps[8];
-    for (int k = 0; k < 8; ++k) eps[k] = 0.f;
+// fp64 arithmetic, fp32 storage.  Bound by the fp64 logarithms and sines: four coordinates per lane
+// share the chunk's K Philox calls, and both values of a Box-Muller pair come from one logarithm,
+// root and sincos.  4 x 2048 x 7168, K = 8: 4.2 ms with one coordinate per lane (which drew each
+// call up to four times and each pair twice), 1.74 ms here; the logits' 1.9 GB alone take 0.3 ms.
+template <int K, int kMode>
+__global__ __launch_bounds__(kBlock) void k_init_logits(const void* W, int w_bf16, const float* S,
+                                                        float* L, uint8_t* J0, int64_t N, int gs,
+                                                        InitConsts ic) {
+  for (int64_t e0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4; e0 < N;
+       e0 += (int64_t)gridDim.x * kBlock * 4) {
+    float w[4];
+    load_w4(W, w_bf16, e0, w);
+    const float s = S[e0 / gs];   // groups are multiples of 16
+    float eps[4 * K];             // flat position q K + k
     if (ic.noise) {
       // flat positions (2m, 2m+1) of the chunk's stream form one Box-Muller pair (cos, sin)
-      const uint64_t e0 = (uint64_t)e & ~(uint64_t)3;
-      const int qq = (int)(e & 3);
-      for (int k = 0; k < ic.K; ++k) {
-        const int f = qq * ic.K + k;
-        const U4 x = noise_words(ic.seed, e0, 0u, 1u, (uint32_t)(f >> 2));
-        const int r0 = f & 2;   // the pair's first word within the call
-        const double u0 = uniform01(word_of(x, r0)), u1 = uniform01(word_of(x, r0 + 1));
-        const double rad = sqrt(-2.0 * log(u0)), ang = 2.0 * M_PI * u1;
-        eps[k] = (float)((f & 1) ? rad * sin(ang) : rad * cos(ang));
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        const U4 x = noise_words(ic.seed, (uint64_t)e0, 0u, 1u, (uint32_t)j);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const double u0 = uniform01(word_of(x, 2 * h)), u1 = uniform01(word_of(x, 2 * h + 1));
+          const double rad = sqrt(-2.0 * log(u0)), ang = 2.0 * M_PI * u1;
+          double sn, cs;
+          sincos(ang, &sn, &cs);
+          eps[4 * j + 2 * h] = (float)(rad * cs);
+          eps[4 * j + 2 * h + 1] = (float)(rad * sn);
+        }
       }
+    } else {
+#pragma unroll
+      for (int f = 0; f < 4 * K; ++f) eps[f] = 0.f;
     }
-    for (int k = 0; k < ic.K; ++k)
-      L[state_off(e, k, ic.K)] =
-          (float)((double)ic.sigma * ((double)eps[k] + (double)ic.alpha * (mu[k] - mean)));
+    float4 out[K];
+    uint32_t j4 = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float u = s != 0.f ? __fdiv_rn(w[i], s) : 0.f;
+      int q = 0;
+      for (int k = 0; k + 1 < ic.n_grid; ++k) q += ((double)u > ic.mids[k]) ? 1 : 0;
+      j4 |= (uint32_t)q << (8 * i);
+      double mu[K], mean = 0.0;
+      if constexpr (kMode == GSQ_RELAX_TERNARY) {
+        mu[0] = q != 1 ? 1.0 : -1.0;
+        mu[1] = (double)(q - 1);
+      } else {
+        double cq = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) if (k == q) cq = (double)ic.c[k];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          const double dlt = kMode == GSQ_RELAX_SHIFT ? (double)(k - 2) : (double)ic.c[k] - cq;
+          mu[k] = -0.5 * dlt * dlt;
+          mean += mu[k];
+        }
+        mean /= (double)K;
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        f4set(out[k], i, (float)((double)ic.sigma *
+                                 ((double)eps[i * K + k] + (double)ic.alpha * (mu[k] - mean))));
+    }
+    if constexpr (kMode == GSQ_RELAX_SHIFT) *reinterpret_cast<uint32_t*>(J0 + e0) = j4;
+#pragma unroll
+    for (int k = 0; k < K; ++k) st_stream(L + state_off(e0, k, K), out[k]);
   }
 }
 
@@ -1075,22 +1135,31 @@ ElemArgs base_args(const Layer& L) {
 
 hipError_t launch_symmetrize_h(const float* Hin, void* Hout, int64_t B, int64_t I, int64_t Ipad,
                                bool bf16, hipStream_t s) {
-  dim3 grid((unsigned)(Ipad / 32), (unsigned)(Ipad / 32), (unsigned)B);
-  hipLaunchKernelGGL(k_symmetrize, grid, dim3(32, 8), 0, s, Hin, Hout, I, Ipad, bf16 ? 1 : 0);
+  // Ipad is a multiple of 256; blocks below the diagonal end at once
+  const dim3 grid((unsigned)(Ipad / kSymT), (unsigned)(Ipad / kSymT), (unsigned)B);
+  if (bf16) hipLaunchKernelGGL(k_symmetrize<true>, grid, dim3(kBlock), 0, s, Hin, Hout, I, Ipad);
+  else hipLaunchKernelGGL(k_symmetrize<false>, grid, dim3(kBlock), 0, s, Hin, Hout, I, Ipad);
   return hipGetLastError();
 }
 
 hipError_t launch_init_scales(const Layer& L, const float* scales_init, float cmax, hipStream_t s) {
   if (L.cfg.layout == GSQ_LAYOUT_SUPERBLOCK) {
     const int64_t nb = L.N / 256;
-    hipLaunchKernelGGL(k_init_scales_superblock, flat_grid(nb), dim3(256), 0, s, L.W, L.w_bf16, L.S,
-                       L.sb_d, L.sb_sc, nb, cmax);
+    hipLaunchKernelGGL(k_init_scales_superblock, flat_grid(nb, kBlock / 64), dim3(kBlock), 0, s, L.W,
+                       L.w_bf16, L.S, L.sb_d, L.sb_sc, nb, cmax);
   } else if (scales_init) {
     return hipMemcpyAsync(L.S, scales_init, L.NG * sizeof(float), hipMemcpyDeviceToDevice, s);
   } else {
-    hipLaunchKernelGGL(k_init_scales_group, flat_grid(L.NG), dim3(256), 0, s, L.W, L.w_bf16, L.S,
-                       L.NG, (int)L.gs, cmax);
+    hipLaunchKernelGGL(k_init_scales_group, flat_grid(L.N, 4 * kBlock), dim3(kBlock), 0, s, L.W,
+                       L.w_bf16, L.S, L.N, (int)L.gs, cmax);
   }
+  return hipGetLastError();
+}
+
+template <int K, int kMode = GSQ_RELAX_GRID>
+static hipError_t init_logits_k(const Layer& L, const InitConsts& ic, hipStream_t s) {
+  hipLaunchKernelGGL((k_init_logits<K, kMode>), flat_grid(L.N, 4 * kBlock), dim3(kBlock), 0, s, L.W,
+                     L.w_bf16, L.S, L.L, L.J0, L.N, (int)L.gs, ic);
   return hipGetLastError();
 }
 
@@ -1100,16 +1169,22 @@ hipError_t launch_init_logits(const Layer& L, const double* mids, hipStream_t s)
     ic.c[k] = k < L.n_grid ? L.cfg.levels[k] : 0.f;
     ic.mids[k] = k + 1 < L.n_grid ? mids[k] : 0.0;
   }
-  ic.K = (int)L.K;
   ic.n_grid = L.n_grid;
-  ic.relax = L.relax;
   ic.alpha = L.cfg.alpha;
   ic.sigma = L.cfg.sigma_init;
   ic.noise = L.cfg.init_noise;
   ic.seed = L.cfg.seed;
-  hipLaunchKernelGGL(k_init_logits, flat_grid(L.N), dim3(256), 0, s, L.W, L.w_bf16, L.S, L.L, L.J0,
-                     L.N, (int)L.gs, ic);
-  return hipGetLastError();
+  if (L.relax == GSQ_RELAX_SHIFT) return init_logits_k<GSQ_SHIFT_WINDOW, GSQ_RELAX_SHIFT>(L, ic, s);
+  if (L.relax == GSQ_RELAX_TERNARY) return init_logits_k<2, GSQ_RELAX_TERNARY>(L, ic, s);
+  switch (L.K) {
+    case 2: return init_logits_k<2>(L, ic, s);
+    case 3: return init_logits_k<3>(L, ic, s);
+    case 4: return init_logits_k<4>(L, ic, s);
+    case 5: return init_logits_k<5>(L, ic, s);
+    case 6: return init_logits_k<6>(L, ic, s);
+    case 7: return init_logits_k<7>(L, ic, s);
+    default: return init_logits_k<8>(L, ic, s);
+  }
 }
 
 template <int K, int kMode = GSQ_RELAX_GRID>

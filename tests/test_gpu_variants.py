@@ -127,3 +127,51 @@ def test_contraction_fp32(dev, B_, O, I):
         Rh = (W[b] - scales[b].repeat_interleave(16, 1) * c[codes[b].long()]).double()
         loss = (Rh * (Rh @ Hb)).sum()
         assert abs(hard[b].double() - loss) <= 2e-6 * loss, (b, hard[b].item(), loss.item())
+
+
+# ------------------------------------------------------------------ initialisation
+# (relaxation, layout, levels, group): four coordinates per lane and 256 per wavefront, with ends
+# inside a wavefront, and every group size
+@pytest.mark.parametrize("relax,layout,K,gs", [
+    ("grid", "group", 2, 16), ("grid", "group", 3, 32), ("grid", "group", 4, 64),
+    ("grid", "group", 5, 128), ("grid", "group", 6, 256), ("grid", "group", 7, 16),
+    ("grid", "group", 8, 128), ("grid", "superblock", 8, 16), ("shift", "group", 8, 64),
+    ("shift", "group", 16, 16), ("ternary", "base3", 3, 32)])
+@pytest.mark.parametrize("B_,O,units", [(1, 1, 1), (2, 5, 3), (1, 70, 5)])
+@pytest.mark.parametrize("prec", ["bf16", "fp32"])
+def test_initial_state(dev, relax, layout, K, gs, B_, O, units, prec):
+    """Scales exactly, logits to their fp32 rounding (the noise's fp64 functions may differ by an
+    ulp of fp64), base indices exactly; a zero group takes the scale 1 (0 in a super-block)."""
+    I = units * (256 if layout == "superblock" else gs)
+    W, H = layer_inputs(O, I, batch=B_, bf16=prec == "bf16", seed=K)
+    W[-1, -1, -gs:] = 0.0
+    rcfg = ref.Config(O, I, _levels(K), gs, batch=B_, precision=prec, seed=11, sigma_init=0.7,
+                      relaxation=relax, layout=layout)
+    got, st = Pair(rcfg, W, H, dev).get(), ref.init_layer(rcfg, W)
+    np.testing.assert_array_equal(got.scales, st.scales)
+    assert rel_err(got.logits, st.logits) <= 2.0 ** -23
+    if relax == "shift":
+        np.testing.assert_array_equal(got.base, st.base)
+    assert not got.m.any() and not got.v.any() and not got.m_s.any() and not got.v_s.any()
+
+
+@pytest.mark.parametrize("B_,I", [(1, 16), (2, 48), (1, 64), (1, 256), (3, 272), (1, 336)])
+@pytest.mark.parametrize("prec", ["bf16", "fp32"])
+def test_symmetrised_h(dev, prec, B_, I):
+    """Rows of G = -2 R H for an H that is not symmetric: (H + H^T) / 2 is formed in fp32 and then
+    rounded to the operand's type, over tiles of 64 with ragged ends."""
+    gen = torch.Generator(device=dev).manual_seed(I)
+    W = torch.randn(B_, 40, I, generator=gen, device=dev) * 0.02
+    H = torch.randn(B_, I, I, generator=gen, device=dev)
+    cfg = B.LayerConfig(40, I, _levels(4), 16, batch=B_, seed=4,
+                        precision=B.PREC_FP32 if prec == "fp32" else B.PREC_BF16)
+    dt = torch.float32 if prec == "fp32" else torch.bfloat16
+    layer = B.Layer(cfg, W.to(dt), H)
+    layer.step(B.StepParams(tau=0.7))
+    R, G = torch.empty(B_, 40, I, device=dev, dtype=dt), torch.empty(B_, 40, I, device=dev)
+    layer.intermediates(R, G)
+    for b in range(B_):
+        Hb = ((H[b] + H[b].t()) * 0.5).to(dt).double()
+        want = -2.0 * (R[b].double() @ Hb)
+        # fp32 sums of at most 336 products
+        assert (G[b].double() - want).norm() <= 4 * 2.0 ** -24 * I ** 0.5 * want.norm()
