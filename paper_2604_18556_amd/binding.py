@@ -24,7 +24,7 @@ STATUS_NAMES = {0: "GSQ_OK", -1: "GSQ_EINVAL", -2: "GSQ_ENOMEM", -3: "GSQ_EHIP",
 
 EXPORTS = ("gsq_layer_init", "gsq_step", "gsq_step_static", "gsq_harden", "gsq_packed_size",
            "gsq_pack", "gsq_get_state", "gsq_set_state", "gsq_get_intermediates", "gsq_gumbel", "gsq_check",
-           "gsq_layer_destroy", "gsq_last_error", "gsq_timing", "gsq_timing_read")
+           "gsq_layer_destroy", "gsq_release_cached", "gsq_last_error", "gsq_timing", "gsq_timing_read")
 KERNEL_NAMES = ("init", "forward", "contract", "reduce", "backward", "harden", "pack")
 
 
@@ -138,12 +138,13 @@ def load(path=None):
     lib.gsq_gumbel.argtypes = [ctypes.POINTER(CConfig), i64, i64, i64, vp, vp]
     lib.gsq_check.argtypes = [vp, vp]
     lib.gsq_layer_destroy.argtypes = [vp]
+    lib.gsq_release_cached.argtypes = []
     lib.gsq_last_error.restype = ctypes.c_char_p
     lib.gsq_timing.argtypes = [vp, i32]
     lib.gsq_timing_read.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64), i32, vp]
     for name in ("gsq_layer_init", "gsq_step", "gsq_step_static", "gsq_harden", "gsq_pack",
                  "gsq_get_state", "gsq_set_state", "gsq_get_intermediates", "gsq_gumbel", "gsq_check",
-                 "gsq_layer_destroy", "gsq_timing", "gsq_timing_read"):
+                 "gsq_layer_destroy", "gsq_release_cached", "gsq_timing", "gsq_timing_read"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib
     return lib
@@ -152,6 +153,11 @@ def load(path=None):
 def _check(status):
     if status != GSQ_OK:
         raise GsqError(status, load().gsq_last_error().decode())
+
+
+def release_cached():
+    """Free the device memory the library keeps from destroyed layers for the next ones."""
+    _check(load().gsq_release_cached())
 
 
 def _ptr(t):

@@ -10,6 +10,7 @@
 #include <string>
 
 #include "gsq_internal.h"
+#include "gsq_pool.h"
 
 namespace {
 
@@ -89,26 +90,42 @@ gsq_status validate_config(const gsq_config* c) {
   return GSQ_OK;
 }
 
-void free_layer(gsq::Layer* L) {
+gsq::DevicePool g_pool;   // at process exit the runtime frees device memory itself
+
+// Free a handle nothing on its device uses any more (`idle`; else its memory is not kept).
+void free_layer(gsq::Layer* L, bool idle) {
   if (!L) return;
   for (auto& p : L->pending) {
     (void)hipEventDestroy(p.second.first);
     (void)hipEventDestroy(p.second.second);
   }
   for (hipEvent_t e : L->event_pool) (void)hipEventDestroy(e);
-  void* bufs[] = {L->W, L->H, L->L, L->M, L->V, L->S, L->MS, L->VS, L->R[0], L->R[1],
-                  L->G, L->partials, L->loss_part, L->loss_stage, L->loss_tickets,
-                  L->flag, L->sb_d, L->sb_sc, L->codes,
-                  L->J0};
-  for (void* p : bufs)
-    if (p) (void)hipFree(p);
+  const size_t limit = idle ? gsq::DevicePool::limit() : 0;
+  for (int i = 0; i < L->n_bufs; ++i) g_pool.give(L->device, L->bufs[i].p, L->bufs[i].bytes, limit);
+  if (L->flag) (void)hipFree(L->flag);
   delete L;
 }
 
+// The handle's buffers, from the kept blocks where one fits.
 template <typename T>
-bool alloc(T** p, size_t bytes) {
+bool alloc(gsq::Layer& L, T** p, size_t bytes) {
   void* q = nullptr;
-  if (hipMalloc(&q, bytes == 0 ? 1 : bytes) != hipSuccess) {
+  size_t got = 0;
+  if (L.n_bufs == gsq::Layer::kMaxBufs ||
+      g_pool.take(L.device, bytes == 0 ? 1 : bytes, &q, &got) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  L.bufs[L.n_bufs++] = {q, got};
+  *p = static_cast<T*>(q);
+  return true;
+}
+
+// One from the runtime itself.
+template <typename T>
+bool alloc_new(T** p, size_t bytes) {
+  void* q = nullptr;
+  if (hipMalloc(&q, bytes) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
@@ -272,30 +289,35 @@ gsq_status gsq_layer_init(const gsq_config* cfg, const void* W, int32_t w_dtype,
       return hip_fail(e, "hipFuncSetAttribute");
     }
   }
-  bool ok = alloc(&L.W, L.N * (L.w_bf16 ? 2 : 4)) &&
-            alloc(&L.H, (size_t)(L.B * L.Ipad * L.Ipad) * relem) &&
-            alloc(&L.L, gsq::state_floats(L) * 4) && alloc(&L.M, gsq::state_floats(L) * 4) &&
-            alloc(&L.V, gsq::state_floats(L) * 4) &&
-            alloc(&L.S, L.NG * 4) && alloc(&L.MS, L.NG * 4) && alloc(&L.VS, L.NG * 4) &&
-            alloc(&L.R[0], npad * relem) && alloc(&L.R[1], npad * relem) &&
-            alloc(&L.G, npad * 4) && alloc(&L.partials, (size_t)(L.B * gsq::contract_partials_per_batch(L)) * 8) &&
-            alloc(&L.loss_part, (size_t)(L.B * L.O * L.loss_cols) * 8) &&
-            alloc(&L.loss_stage, (size_t)gsq::loss_stage_size(L) * 8) &&
-            alloc(&L.loss_tickets, (size_t)L.B * sizeof(unsigned)) &&
-            alloc(&L.flag, sizeof(int)) && alloc(&L.codes, (size_t)L.N);
+  // the flag comes from the runtime on every call, so that what refuses an allocation (a stream
+  // capture) refuses a handle too, whatever is kept
+  bool ok = alloc_new(&L.flag, sizeof(int)) &&
+            alloc(L, &L.W, L.N * (L.w_bf16 ? 2 : 4)) &&
+            alloc(L, &L.H, (size_t)(L.B * L.Ipad * L.Ipad) * relem) &&
+            alloc(L, &L.L, gsq::state_floats(L) * 4) && alloc(L, &L.M, gsq::state_floats(L) * 4) &&
+            alloc(L, &L.V, gsq::state_floats(L) * 4) &&
+            alloc(L, &L.S, L.NG * 4) && alloc(L, &L.MS, L.NG * 4) && alloc(L, &L.VS, L.NG * 4) &&
+            alloc(L, &L.R[0], npad * relem) && alloc(L, &L.R[1], npad * relem) &&
+            alloc(L, &L.G, npad * 4) && alloc(L, &L.partials, (size_t)(L.B * gsq::contract_partials_per_batch(L)) * 8) &&
+            alloc(L, &L.loss_part, (size_t)(L.B * L.O * L.loss_cols) * 8) &&
+            alloc(L, &L.loss_stage, (size_t)gsq::loss_stage_size(L) * 8) &&
+            alloc(L, &L.loss_tickets, (size_t)L.B * sizeof(unsigned)) &&
+            alloc(L, &L.codes, (size_t)L.N);
   if (ok && cfg->layout == GSQ_LAYOUT_SUPERBLOCK)
-    ok = alloc(&L.sb_d, (L.N / 256) * 2) && alloc(&L.sb_sc, L.N / 16);
-  if (ok && cfg->relaxation == GSQ_RELAX_SHIFT) ok = alloc(&L.J0, (size_t)L.N);
+    ok = alloc(L, &L.sb_d, (L.N / 256) * 2) && alloc(L, &L.sb_sc, L.N / 16);
+  if (ok && cfg->relaxation == GSQ_RELAX_SHIFT) ok = alloc(L, &L.J0, (size_t)L.N);
   if (!ok) {
-    free_layer(h);
+    free_layer(h, true);   // nothing was enqueued
     return fail(GSQ_ENOMEM, "device allocation failed for a %lld x %lld x %lld layer",
                 (long long)L.B, (long long)L.O, (long long)L.I);
   }
   auto run = [&]() -> gsq_status {
     GSQ_HIP(hipMemcpyAsync(L.W, W, L.N * (L.w_bf16 ? 2 : 4), hipMemcpyDeviceToDevice, stream));
     GSQ_HIP(timed(L, GSQ_KERNEL_INIT, stream, [&] { return gsq::launch_symmetrize_h(H, L.H, L.B, L.I, L.Ipad, L.bf16, stream); }));
-    GSQ_HIP(hipMemsetAsync(L.R[0], 0, npad * relem, stream));   // padding stays zero
-    GSQ_HIP(hipMemsetAsync(L.R[1], 0, npad * relem, stream));
+    if (L.Opad != L.O || L.Ipad != L.I) {   // padding stays zero; the rest is written before use
+      GSQ_HIP(hipMemsetAsync(L.R[0], 0, npad * relem, stream));
+      GSQ_HIP(hipMemsetAsync(L.R[1], 0, npad * relem, stream));
+    }
     GSQ_HIP(hipMemsetAsync(L.M, 0, gsq::state_floats(L) * 4, stream));
     GSQ_HIP(hipMemsetAsync(L.V, 0, gsq::state_floats(L) * 4, stream));
     GSQ_HIP(hipMemsetAsync(L.MS, 0, L.NG * 4, stream));
@@ -313,8 +335,7 @@ gsq_status gsq_layer_init(const gsq_config* cfg, const void* W, int32_t w_dtype,
   };
   st = run();
   if (st != GSQ_OK) {
-    (void)hipStreamSynchronize(stream);
-    free_layer(h);
+    free_layer(h, hipStreamSynchronize(stream) == hipSuccess);
     return st;
   }
   {
@@ -330,14 +351,17 @@ gsq_status gsq_layer_init(const gsq_config* cfg, const void* W, int32_t w_dtype,
 // Room for M per-sample gradients (a step asking for more samples than any before it); the
 // old buffer is released after the device is idle.
 static gsq_status grow_sample_slots(gsq::Layer& L, int M) {
-  const size_t npad = (size_t)(L.B * L.Opad * L.Ipad);
+  const size_t npad = (size_t)(L.B * L.Opad * L.Ipad), bytes = (size_t)M * npad * 4;
   float* G = nullptr;
-  if (!alloc(&G, (size_t)M * npad * 4)) return fail(GSQ_ENOMEM, "no room for %d samples", M);
+  if (!alloc_new(&G, bytes) && !(g_pool.release(L.device) && alloc_new(&G, bytes)))
+    return fail(GSQ_ENOMEM, "no room for %d samples", M);
   const hipError_t e = hipDeviceSynchronize();   // no launch on any stream still reads the old one
   if (e != hipSuccess) {
     (void)hipFree(G);
     return hip_fail(e, "hipDeviceSynchronize");
   }
+  for (int i = 0; i < L.n_bufs; ++i)
+    if (L.bufs[i].p == L.G) L.bufs[i] = {G, bytes};
   (void)hipFree(L.G);
   L.G = G;
   L.sample_slots = M;
@@ -641,8 +665,20 @@ gsq_status gsq_check(gsq_layer* h, hipStream_t stream) {
 
 gsq_status gsq_layer_destroy(gsq_layer* h) {
   if (!h) return GSQ_OK;
-  (void)hipDeviceSynchronize();
-  free_layer(h);
+  // its own device must be idle (and be the current one, as the kept blocks' limit is)
+  int dev = -1;
+  const int h_device = h->device;
+  const bool own = hipGetDevice(&dev) == hipSuccess &&
+                   (dev == h_device || hipSetDevice(h_device) == hipSuccess);
+  const bool idle = hipDeviceSynchronize() == hipSuccess;
+  free_layer(h, own && idle);
+  if (own && dev != h_device) (void)hipSetDevice(dev);
+  return GSQ_OK;
+}
+
+gsq_status gsq_release_cached(void) {
+  g_err.clear();
+  g_pool.release(-1);
   return GSQ_OK;
 }
 

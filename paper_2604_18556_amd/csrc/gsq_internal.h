@@ -83,6 +83,10 @@ struct Layer {
   uint8_t* sb_sc = nullptr;
   uint8_t* codes = nullptr;
   uint8_t* J0 = nullptr;       // local shift: initial grid indices
+  // what the handle owns besides the flag, for its end
+  static constexpr int kMaxBufs = 24;
+  struct { void* p; size_t bytes; } bufs[kMaxBufs];
+  int n_bufs = 0;
   int64_t t = 0;
   int device = 0;         // HIP device the handle was created on
   int cur = 0;            // R buffer holding a prepared sample (when r_valid)

@@ -175,3 +175,60 @@ def test_symmetrised_h(dev, prec, B_, I):
         want = -2.0 * (R[b].double() @ Hb)
         # fp32 sums of at most 336 products
         assert (G[b].double() - want).norm() <= 4 * 2.0 ** -24 * I ** 0.5 * want.norm()
+
+
+# ------------------------------------------------------------------ memory kept between handles
+@pytest.mark.parametrize("prec", ["bf16", "fp32"])
+def test_layers_from_kept_memory(dev, prec):
+    """A layer made of memory that other layers left behind gives the bits of the same layer made
+    of fresh memory: shapes that fit the kept blocks exactly, with a margin, and not at all, with
+    padding where the block's last user had data, on another stream, and with more samples."""
+    def life(O, I, relax, stream=None, samples=1):
+        W, H = layer_inputs(O, I, bf16=prec == "bf16", seed=O)
+        rcfg = ref.Config(O, I, _levels(8), 16, precision=prec, seed=O, relaxation=relax)
+        with torch.cuda.stream(stream or torch.cuda.current_stream()):
+            pair = Pair(rcfg, W, H, dev)
+            for t in range(2):
+                loss = pair.step(B.StepParams(tau=0.9, tau_next=0.9, samples=samples))
+            st, inter = pair.get(), pair.intermediates()
+            codes = torch.empty(1, O, I, dtype=torch.uint8, device=dev)
+            hard = torch.zeros(1, device=dev)
+            pair.layer.harden(codes=codes, hard_loss=hard)
+            out = [loss, st.logits, st.m, st.v, st.scales, *inter, codes.cpu().numpy(),
+                   hard.cpu().numpy()]
+            pair.layer.destroy()
+        return out
+
+    shapes = [(300, 272, "grid"), (256, 256, "grid"), (290, 272, "shift"), (40, 1040, "grid"),
+              (512, 512, "grid"), (300, 272, "grid")]
+    fresh = []
+    for s in shapes:
+        B.release_cached()
+        fresh.append(life(*s))
+    B.release_cached()
+    other = torch.cuda.Stream()
+    for n, k in enumerate([4, 0, 1, 2, 0, 3, 5, 0, 4, 2]):
+        if n == 4:
+            life(300, 272, "grid", samples=3)   # its larger G is left behind too
+        for x, y in zip(life(*shapes[k], stream=other if n % 2 else None), fresh[k]):
+            np.testing.assert_array_equal(x, y, err_msg=f"shape {shapes[k]}, use {n}")
+
+
+def test_kept_memory_is_bounded_and_given_back(dev):
+    """Ended handles keep at most a sixteenth of the device's memory; release_cached frees it."""
+    B.release_cached()
+    torch.cuda.synchronize()
+    free0, total = torch.cuda.mem_get_info()
+    H = torch.eye(256, device=dev).reshape(1, 256, 256)
+    for O in (4096, 400_000, 4096):   # 8 levels: 27 MB per 1024 rows and array; 10 GB for the second
+        W = torch.zeros(1, O, 256, device=dev, dtype=torch.bfloat16)
+        layers = [B.Layer(B.LayerConfig(O, 256, _levels(8), 128), W, H) for _ in range(3)]
+        for x in layers:
+            x.destroy()
+        del W, x, layers
+        torch.cuda.empty_cache()
+        kept = free0 - torch.cuda.mem_get_info()[0]
+        assert kept <= total / 16 + (64 << 20), kept
+    assert kept > 0
+    B.release_cached()
+    assert free0 - torch.cuda.mem_get_info()[0] <= 64 << 20
