@@ -14,7 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libgsq.so")
-SOURCES = ["gsq_api.hip", "gsq_elem.hip", "gsq_contract.hip"]
+SOURCES = ["gsq_api.hip", "gsq_elem.hip", "gsq_elem64.hip", "gsq_contract.hip"]
 
 # -packed-fp32-ops: keep the compiler from emitting packed fp32 arithmetic
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

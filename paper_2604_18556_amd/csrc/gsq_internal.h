@@ -110,6 +110,9 @@ hipError_t launch_init_scales(const Layer& L, const float* scales_init, float cm
 hipError_t launch_init_logits(const Layer& L, const double* mids, hipStream_t s);
 hipError_t launch_forward(const Layer& L, const ElemArgs& a, hipStream_t s);
 hipError_t launch_backward(const Layer& L, const ElemArgs& a, bool update_scales, hipStream_t s);
+// the same in fp64, for the FP32 precision (gsq_elem64.hip)
+hipError_t launch_forward_f64(const Layer& L, const ElemArgs& a, hipStream_t s);
+hipError_t launch_backward_f64(const Layer& L, const ElemArgs& a, bool update_scales, hipStream_t s);
 hipError_t launch_harden(const Layer& L, uint8_t* codes, void* Rh, hipStream_t s);
 hipError_t launch_eff_scales(const Layer& L, float* out, hipStream_t s);
 hipError_t launch_pack(const Layer& L, const uint8_t* codes, uint8_t* out, hipStream_t s);

@@ -177,6 +177,40 @@ def test_symmetrised_h(dev, prec, B_, I):
         assert (G[b].double() - want).norm() <= 4 * 2.0 ** -24 * I ** 0.5 * want.norm()
 
 
+# ------------------------------------------------------------------ fp64 backward
+# one coordinate per lane, 256 columns per workgroup: groups inside a wavefront and across two and
+# four, rows that end inside a wavefront, every number of Philox words per coordinate
+@pytest.mark.parametrize("relax,K,gs,I", [
+    ("grid", 2, 16, 16), ("grid", 2, 128, 384), ("grid", 3, 256, 512), ("grid", 4, 64, 320),
+    ("grid", 5, 128, 128), ("grid", 5, 32, 96), ("grid", 6, 256, 256), ("grid", 7, 128, 640),
+    ("grid", 7, 16, 272), ("grid", 8, 256, 768), ("shift", 8, 128, 384), ("shift", 16, 64, 64),
+    ("ternary", 3, 128, 256), ("ternary", 3, 32, 288)])
+@pytest.mark.parametrize("opt,samples", [(B.OPT_ADAM, 1), (B.OPT_LION, 1), (B.OPT_ADAM, 3)])
+@pytest.mark.parametrize("loss", [True, False])
+def test_fp64_steps(dev, relax, K, gs, I, opt, samples, loss):
+    """Two steps, the second from the sample that the first drew, against the oracle: the same fp64
+    arithmetic up to the order of sums, stored in fp32 (2^-24, and the same again in the second
+    step's inputs).  A sign that flips within the rounding of a zero gradient is told apart."""
+    W, H = layer_inputs(7, I, batch=2, bf16=False, seed=K)
+    rcfg = ref.Config(7, I, _levels(K), gs, batch=2, precision="fp32", seed=5, relaxation=relax,
+                      layout="base3" if relax == "ternary" else "group")
+    pair = Pair(rcfg, W, H, dev)
+    st = ref.init_layer(rcfg, W)
+    rng = np.random.default_rng(I)
+    st.m = (rng.standard_normal(st.m.shape) * 1e-3).astype(np.float32)
+    st.v = (rng.uniform(0.5, 2, st.v.shape) * 1e-6).astype(np.float32)
+    pair.put(st)
+    for t in range(2):
+        prm = B.StepParams(tau=0.6 - 0.1 * t, kappa=1.1, tau_next=0.5, kappa_next=1.1, optimizer=opt,
+                           samples=samples, lr_scales=5e-5, weight_decay=0.01)
+        got = pair.step(prm, want_loss=loss)
+        st, want, inter = ref.step(rcfg, W, pair.Hs, st, oracle_params(prm), want=True)
+        if loss:
+            assert np.all(np.abs(got - want) <= 1e-6 * np.abs(want)), (t, got, want)
+        assert_state_close(pair.get(), st, inter["G"], 1e-6, st.t, label=f"step {t}",
+                           dlogits=inter["dlogits"])
+
+
 # ------------------------------------------------------------------ memory kept between handles
 @pytest.mark.parametrize("prec", ["bf16", "fp32"])
 def test_layers_from_kept_memory(dev, prec):
