@@ -3,7 +3,7 @@
 // the loss tr(R H R^T) = sum(R * P) (Eq. 1 for a linear layer, H = X^T X).
 //
 // BF16 precision: R and H in bf16, products accumulated in fp32 on the matrix cores
-// (v_mfma 32x32x16 bf16).  Because H is symmetric, column i of H is row i, so both operands
+// (v_mfma 16x16x32 bf16).  Because H is symmetric, column i of H is row i, so both operands
 // are read along their contiguous dimension.
 // FP32 precision: fp32 operands, fp64 accumulation on the vector units.
 #include <hip/hip_runtime.h>
@@ -17,7 +17,7 @@ namespace gsq {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = kTileM, BN = kTileN, BK = 64;
 constexpr int ROW_BYTES = BK * 2;    // one 64-wide bf16 row: a full cache line
@@ -33,7 +33,7 @@ struct Piece {
   static constexpr int A_SLAB = TM * ROW_BYTES, B_SLAB = TN * ROW_BYTES;
   static constexpr int B_BASE = A_STAGES * A_SLAB;
   static constexpr int A_LOADS = TM / 32, B_LOADS = TN / 32;   // 1 KB loads per wavefront and slab
-  static constexpr int MI = TM / 64, NJ = TN / 64;             // 32 x 32 blocks per wavefront
+  static constexpr int MI = TM / 32, NJ = TN / 32;             // 16 x 16 blocks per wavefront
   static_assert(B_BASE + B_STAGES * B_SLAB <= (int)LDS_BYTES, "the ring fits the LDS");
 };
 // The whole tile uses all the LDS; the smaller pieces, whose slabs last less long, load further
@@ -148,13 +148,6 @@ __device__ __forceinline__ void load_rows(const uint16_t* src, uint8_t* lds) {
   __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
 }
 
-template <int n>
-__device__ __forceinline__ void load_slab(const uint16_t* src, const uint32_t (&off)[n],
-                                          uint8_t* lds_wave) {
-#pragma unroll
-  for (int j = 0; j < n; ++j) load_rows(src + off[j], lds_wave + j * 8 * ROW_BYTES);
-}
-
 // Lane offsets of those copies: row n 8 wave + 8 j + lane / 8, swizzled 16-byte chunk.
 template <int n>
 __device__ __forceinline__ void slab_offsets(uint32_t (&off)[n], int wave, int lane, int64_t Ipad) {
@@ -189,37 +182,44 @@ __device__ __forceinline__ void slab_barrier() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
-// scheduling-group masks
-constexpr int SG_MFMA = 0x008, SG_VMEM = 0x020, SG_DSR = 0x100;
+// One block's product: G's columns are the instruction's rows, so that a lane's four results are
+// four consecutive columns of a row.
+//
+// The instruction is written out because the builtin gives its result other registers than its
+// accumulator input once there are 64 of these, and moves them around.  What the compiler then
+// does not see is the time an accumulator takes to be readable by anything but another product:
+// acc_settled() waits for it, before the first product and after the last.
+__device__ __forceinline__ void mfma_16x16x32(f32x4& acc, const bf16x8& h, const bf16x8& r) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(h), "v"(r));
+}
 
-// Interleave one half-slab's M MFMAs with its R fragment reads and V slab loads: the reads first,
-// one per MFMA where there are enough MFMAs (the whole tile) and two where not, then one load per
-// MFMA, then the MFMAs left.
-template <int M, int R, int V>
-__device__ __forceinline__ void sched_half() {
-  constexpr int kReads = R + V <= M ? 1 : 2;
-  static_assert(R % kReads == 0 && R / kReads + V <= M, "every read and load has its MFMA");
+template <int MI, int NJ>
+__device__ __forceinline__ void acc_settled(f32x4 (&acc)[MI][NJ]) {
+  // accumulators written before this are written before the wait, and read after it
 #pragma unroll
-  for (int i = 0; i < R / kReads; ++i) {
-    __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(SG_DSR, kReads, 0);
-  }
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-  for (int i = 0; i < V; ++i) {
-    __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(SG_VMEM, 1, 0);
-  }
-  if constexpr (M - R / kReads - V > 0)
-    __builtin_amdgcn_sched_group_barrier(SG_MFMA, M - R / kReads - V, 0);
+    for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
+  asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
 }
 
 // One piece of G per workgroup; four wavefronts each own a quarter of it (128 x 128 of a whole
-// tile) as MFMA 32x32x16 blocks.  K slabs 64 wide (whole 128-byte lines of R and H) move by direct
+// tile) as MFMA 16x16x32 blocks.  K slabs 64 wide (whole 128-byte lines of R and H) move by direct
 // global->LDS loads (16 bytes per lane, no staging registers) into the two rings.  R's extra
 // buffer lets its slab k + AHEAD be loaded during the first half of slab k, H's during the second:
-// the loads split evenly between the halves.  The steady-state loop has no branches, so the
-// fragment reads and slab loads are spread between the matrix-core instructions (scheduling
-// groups) instead of stalling them.
+// the loads split evenly between the halves.  The steady-state loop has no branches, and the
+// fragment reads and slab loads are spread between the matrix-core instructions instead of
+// stalling them.
+//
+// Bound by the power that the matrix cores may draw.  With random operands in registers, the
+// 16x16x32 form holds 2090 TFLOP/s on this chip and the 32x32x16 form 1824: half the accumulator
+// traffic per product lets the clock stay higher.  From 32x32x16 to 16x16x32 with the order below:
+// 4096 x 14336 1338 -> 1212 us (1.39 PFLOP/s), 8192 x 28672 10.1 -> 9.24 ms (1.46), 4096 x 4096
+// 132 -> 124 us, 16 x 2048 x 7168 2.66 -> 2.47 ms.
 template <class P>
 __device__ __forceinline__ void contract_piece(const uint16_t* A, const uint16_t* Bt, float* Gp,
                                                const uint16_t* Rp, double* partial, int64_t Ipad,
@@ -228,108 +228,120 @@ __device__ __forceinline__ void contract_piece(const uint16_t* A, const uint16_t
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  f32x16 acc[P::MI][P::NJ];
+  f32x4 acc[P::MI][P::NJ];
 #pragma unroll
   for (int i = 0; i < P::MI; ++i)
 #pragma unroll
-    for (int j = 0; j < P::NJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < P::NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  acc_settled(acc);
 
   uint32_t offa[P::A_LOADS], offb[P::B_LOADS];
   slab_offsets(offa, wave, lane, Ipad);
   slab_offsets(offb, wave, lane, Ipad);   // the same registers where the counts agree
-#define GSQ_ISSUE_A(K)                                                                   \
-  load_slab(A + (int64_t)(K) * BK, offa,                                                 \
-            smem + ((K) % P::A_STAGES) * P::A_SLAB + wave * (P::TM / 4) * ROW_BYTES)
-#define GSQ_ISSUE_B(K)                                                                   \
-  load_slab(Bt + (int64_t)(K) * BK, offb,                                                \
-            smem + P::B_BASE + ((K) % P::B_STAGES) * P::B_SLAB + wave * (P::TN / 4) * ROW_BYTES)
-  const int frow_a = wm * (P::TM / 2) + (lane & 31), frow_b = wn * (P::TN / 2) + (lane & 31);
-  const int fchunk = lane >> 5;
+  uint8_t* const a_wave = smem + wave * (P::TM / 4) * ROW_BYTES;
+  uint8_t* const b_wave = smem + P::B_BASE + wave * (P::TN / 4) * ROW_BYTES;
+  const int frow_a = wm * (P::TM / 2) + (lane & 15), frow_b = wn * (P::TN / 2) + (lane & 15);
+  const int fchunk = lane >> 4;
 
-// fragments of sub-steps 2 HALF and 2 HALF + 1 of slab K into register set S
-#define GSQ_READ(S, K, HALF)                                                             \
-  do {                                                                                   \
-    const uint8_t* As_ = smem + ((K) % P::A_STAGES) * P::A_SLAB;                         \
-    const uint8_t* Bs_ = smem + P::B_BASE + ((K) % P::B_STAGES) * P::B_SLAB;             \
-    _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                      \
-      const int c_ = (2 * (HALF) + h) * 2 + fchunk;                                      \
-      _Pragma("unroll") for (int i = 0; i < P::MI; ++i) {                                \
-        S##a[h][i] = read_frag(As_, frow_a + i * 32, c_);                                \
-        if (i < P::NJ) S##b[h][i] = read_frag(Bs_, frow_b + i * 32, c_);                 \
-      }                                                                                  \
-    }                                                                                    \
-  } while (0)
-#define GSQ_MFMA(S)                                                                      \
-  _Pragma("unroll") for (int h = 0; h < 2; ++h)                                          \
-    _Pragma("unroll") for (int i = 0; i < P::MI; ++i)                                    \
-      _Pragma("unroll") for (int j = 0; j < P::NJ; ++j)                                  \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(S##a[h][i], S##b[h][j], acc[i][j], 0, 0, 0)
-  constexpr int kMfma = 2 * P::MI * P::NJ, kReads = 2 * (P::MI + P::NJ);
+  // load j of this wavefront's share of slab k
+  const auto load_a = [&](int k, int j) {
+    load_rows(A + (int64_t)k * BK + offa[j], a_wave + (k % P::A_STAGES) * P::A_SLAB + j * 8 * ROW_BYTES);
+  };
+  const auto load_b = [&](int k, int j) {
+    load_rows(Bt + (int64_t)k * BK + offb[j], b_wave + (k % P::B_STAGES) * P::B_SLAB + j * 8 * ROW_BYTES);
+  };
+  // fragments of half a slab (32 of K): one read of each of R's and H's blocks in turn
+  constexpr int kMfma = P::MI * P::NJ, kReads = P::MI + P::NJ;
+  const auto read = [&](bf16x8 (&fa)[P::MI], bf16x8 (&fb)[P::NJ], int k, int half, int n) {
+    const int i = n < 2 * P::NJ ? n / 2 : n - P::NJ;
+    if (n < 2 * P::NJ && n % 2)
+      fb[i] = read_frag(smem + P::B_BASE + (k % P::B_STAGES) * P::B_SLAB, frow_b + i * 16, half * 4 + fchunk);
+    else
+      fa[i] = read_frag(smem + (k % P::A_STAGES) * P::A_SLAB, frow_a + i * 16, half * 4 + fchunk);
+  };
   static_assert(P::MI >= P::NJ, "the fragment reads walk R's blocks");
+  // The products of one half, and between them, one at a time, the fragment reads of the next half
+  // and the slab loads: a load after every two reads.  The products have side effects for the
+  // compiler, so this order stays.  Blocks are walked back and forth: one operand of each product
+  // is the last one's.  At 4096 x 14336: 1212 us so, 1270 with all reads before the loads, 1229 with
+  // the loads first, 1228 spread evenly over the half, 1351 one product apart instead of two; 1216
+  // along R's blocks instead of H's.
+  const auto half_slab = [&](const bf16x8 (&fa)[P::MI], const bf16x8 (&fb)[P::NJ], int n_loads,
+                             auto&& next_read, auto&& next_load) {
+    constexpr int kLoads = P::A_LOADS > P::B_LOADS ? P::A_LOADS : P::B_LOADS;
+    constexpr int kOps = kReads + kReads / 2 > 3 * kLoads ? kReads + kReads / 2 : 3 * kLoads;
+    constexpr int kStep = kMfma / kOps;
+    static_assert(kStep >= 1, "every read and load has its product");
+#pragma unroll
+    for (int n = 0; n < kMfma; ++n) {
+      const int i = n / P::NJ, j = i % 2 ? P::NJ - 1 - n % P::NJ : n % P::NJ;
+      mfma_16x16x32(acc[i][j], fb[j], fa[i]);
+      if (n % kStep == 0) {
+        const int o = n / kStep;
+        if (o % 3 == 2) { if (o / 3 < n_loads) next_load(o / 3); }
+        else if (o - o / 3 < kReads) next_read(o - o / 3);
+      }
+    }
+  };
+  const auto none = [](int) {};
 
-  // p: first half (sub-steps 0, 1) of the current slab; q: second half (sub-steps 2, 3)
-  bf16x8 pa[2][P::MI], pb[2][P::NJ], qa[2][P::MI], qb[2][P::NJ];
+  // p: first half of the current slab; q: second half
+  bf16x8 pa[P::MI], pb[P::NJ], qa[P::MI], qb[P::NJ];
 #pragma unroll
   for (int k = 0; k < P::AHEAD; ++k) {
-    GSQ_ISSUE_A(k);
-    GSQ_ISSUE_B(k);
+#pragma unroll
+    for (int j = 0; j < P::A_LOADS; ++j) load_a(k, j);
+#pragma unroll
+    for (int j = 0; j < P::B_LOADS; ++j) load_b(k, j);
   }
   constexpr int kSlabLoads = P::A_LOADS + P::B_LOADS;
   wait_vm<(P::AHEAD - 1) * kSlabLoads>();
   slab_barrier();
-  GSQ_READ(p, 0, 0);
+#pragma unroll
+  for (int n = 0; n < kReads; ++n) read(pa, pb, 0, 0, n);
   // steady state: R's slab kt + AHEAD is loaded during the first half of slab kt (its buffer last
   // held slab kt - 1), H's during the second half (its buffer held slab kt, read by then)
   for (int kt = 0; kt < nk - P::AHEAD; ++kt) {
-    GSQ_READ(q, kt, 1);
-    GSQ_ISSUE_A(kt + P::AHEAD);
-    GSQ_MFMA(p);
-    sched_half<kMfma, kReads, P::A_LOADS>();
+    half_slab(pa, pb, P::A_LOADS, [&](int n) { read(qa, qb, kt, 1, n); },
+              [&](int j) { load_a(kt + P::AHEAD, j); });
     __builtin_amdgcn_sched_barrier(0);   // every MFMA of this half is issued before the wait
     // slab kt + 1 has landed (later ones, of kt + AHEAD only R's, may be in flight), and every
     // wavefront has read slab kt
     wait_vm<(P::AHEAD - 2) * kSlabLoads + P::A_LOADS>();
     slab_barrier();
-    GSQ_READ(p, kt + 1, 0);
-    GSQ_ISSUE_B(kt + P::AHEAD);
-    GSQ_MFMA(q);
-    sched_half<kMfma, kReads, P::B_LOADS>();
+    half_slab(qa, qb, P::B_LOADS, [&](int n) { read(pa, pb, kt + 1, 0, n); },
+              [&](int j) { load_b(kt + P::AHEAD, j); });
     __builtin_amdgcn_sched_barrier(0);
   }
   // the last slabs: nothing more to load
   for (int kt = nk - P::AHEAD; kt < nk - 1; ++kt) {
-    GSQ_READ(q, kt, 1);
-    GSQ_MFMA(p);
+    half_slab(pa, pb, 0, [&](int n) { read(qa, qb, kt, 1, n); }, none);
     wait_vm<0>();
     slab_barrier();
-    GSQ_READ(p, kt + 1, 0);
-    GSQ_MFMA(q);
+    half_slab(qa, qb, 0, [&](int n) { read(pa, pb, kt + 1, 0, n); }, none);
   }
-  GSQ_READ(q, nk - 1, 1);
-  GSQ_MFMA(p);
-  GSQ_MFMA(q);
-#undef GSQ_MFMA
-#undef GSQ_READ
-#undef GSQ_ISSUE_A
-#undef GSQ_ISSUE_B
+  half_slab(pa, pb, 0, [&](int n) { read(qa, qb, nk - 1, 1, n); }, none);
+  half_slab(qa, qb, 0, none, none);
+  acc_settled(acc);
 
   // G = -2 P and, on request, the piece's loss partial sum(R P).
-  // 32 x 32 accumulator layout: lane l, register r -> row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+  // 16 x 16 block: lane l holds row l % 16 and columns 4 (l / 16) .. + 3.
   double lsum = 0.0;
 #pragma unroll
   for (int i = 0; i < P::MI; ++i)
 #pragma unroll
-    for (int j = 0; j < P::NJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = wm * (P::TM / 2) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int64_t col = wn * (P::TN / 2) + j * 32 + (lane & 31);
-        const float p = acc[i][j][r];
-        Gp[row * Ipad + col] = -2.f * p;
-        if (want_loss) lsum += (double)bf16_to_f32(Rp[row * Ipad + col]) * (double)p;
+    for (int j = 0; j < P::NJ; ++j) {
+      const int64_t at = (int64_t)(frow_a + i * 16) * Ipad + wn * (P::TN / 2) + j * 16 + 4 * (lane >> 4);
+      const f32x4 p = acc[i][j];
+      *reinterpret_cast<f32x4*>(Gp + at) = -2.f * p;
+      if (want_loss) {
+        const uint2 r = *reinterpret_cast<const uint2*>(Rp + at);
+        lsum += (double)bf16_to_f32((uint16_t)r.x) * (double)p[0];
+        lsum += (double)bf16_to_f32((uint16_t)(r.x >> 16)) * (double)p[1];
+        lsum += (double)bf16_to_f32((uint16_t)r.y) * (double)p[2];
+        lsum += (double)bf16_to_f32((uint16_t)(r.y >> 16)) * (double)p[3];
       }
+    }
   if (want_loss) block_sum_to(lsum, partial, reinterpret_cast<double*>(smem));
 }
 
@@ -421,7 +433,6 @@ unsigned plan_grid(const Layer& L, const Plan& pl) {
 // at 4 (l / 16), one for each of four MFMAs: the same k on both sides, in another order than
 // memory's.  Result: lane l, register r -> row 4 r + l / 16, column l % 16.
 constexpr int SK = 32, SK_ROW = SK + 4;
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 template <int W>
