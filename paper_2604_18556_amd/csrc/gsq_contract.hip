@@ -526,56 +526,75 @@ int f32_tile(const Layer& L) {
 }
 
 // Loss of layer b = scale * the sum of its per_batch partials, in a fixed order, in one launch:
-// block (c, b) sums chunk c (kChunk consecutive partials) into stage[b * nchunks + c]; the last
-// block of layer b to finish (a ticket counter, reset by that block) sums the chunks in order.
+// block (c, b) sums chunk c (kChunk consecutive partials); where there are more chunks, into
+// stage[b * nchunks + c], and the last block of layer b to finish (a ticket counter, reset by that
+// block) sums the chunks in order.  Bound by latency: wavefront sums in registers and one exchange
+// through LDS instead of a tree of eight barriers, chunks of 8192 instead of 2048, so that up to
+// 8192 partials need no hand-over, and a hand-over without a fence.  256 x 256: 4.1 -> 1.9 us,
+// 1024 x 4096: 6.0 -> 5.3 (8.2 with the fence), 4096 x 4096: 7.2 -> 5.3.
 constexpr int kPer = 8;                 // partials per thread, all loaded before summing
-constexpr int kChunk = 256 * kPer;
+constexpr int kReduceBlock = 1024;
+constexpr int kChunk = kReduceBlock * kPer;
 
-__device__ __forceinline__ double block_tree_sum(double x) {
-  __shared__ double red[256];
-  red[threadIdx.x] = x;
+// Sum over the workgroup, left in thread 0.
+__device__ __forceinline__ double reduce_block_sum(double x) {
+  __shared__ double red[kReduceBlock / 64];
+  x = wave_sum_to_lane63(x);
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = x;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  double r = 0.0;
+  if (threadIdx.x < 64) {
+    r = wave_sum_to_lane63(threadIdx.x < kReduceBlock / 64 ? red[threadIdx.x] : 0.0);
+    r = __shfl(r, 63, 64);
   }
-  const double r = red[0];
-  __syncthreads();
+  __syncthreads();   // red may be used again
   return r;
 }
 
-__global__ void k_reduce_loss(const double* partials, int64_t per_batch, int nchunks,
-                              double* stage, unsigned* tickets, double scale, float* loss_out,
-                              int* flag) {
+__global__ __launch_bounds__(kReduceBlock) void k_reduce_loss(const double* partials,
+                                                              int64_t per_batch, int nchunks,
+                                                              double* stage, unsigned* tickets,
+                                                              double scale, float* loss_out,
+                                                              int* flag) {
   const int64_t b = blockIdx.y, c = blockIdx.x;
   const int64_t lo = c * kChunk, hi = min(per_batch, lo + kChunk);
   double v[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const int64_t i = lo + threadIdx.x + 256 * j;
+    const int64_t i = lo + threadIdx.x + kReduceBlock * j;
     v[j] = i < hi ? partials[b * per_batch + i] : 0.0;
   }
   double s = 0.0;
 #pragma unroll
   for (int j = 0; j < kPer; ++j) s += v[j];
-  const double tot = block_tree_sum(s);
-  __shared__ unsigned ticket;
-  if (threadIdx.x == 0) {
-    stage[b * nchunks + c] = tot;
-    __threadfence();                       // the chunk sum is visible before the ticket
-    ticket = atomicAdd(&tickets[b], 1u);
+  double all = reduce_block_sum(s);
+  if (nchunks > 1) {   // the same for the whole grid
+    __shared__ unsigned ticket;
+    if (threadIdx.x == 0) {
+      // The chunk sum goes to where every XCD sees it, and the ticket is drawn once that has
+      // answered: both are device-wide read-modify-writes, and the second needs the first's result.
+      // A fence instead would write back the XCD's whole L2, full of the backward's output.
+      const uint64_t old = __hip_atomic_exchange(reinterpret_cast<uint64_t*>(stage) + b * nchunks + c,
+                                                 (uint64_t)__double_as_longlong(all),
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned one = 1u;
+      asm volatile("" : "+v"(one) : "v"(old) : "memory");
+      ticket = __hip_atomic_fetch_add(&tickets[b], one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (ticket != (unsigned)(nchunks - 1)) return;
+    double t = 0.0;
+    for (int i = threadIdx.x; i < nchunks; i += kReduceBlock)
+      t += __longlong_as_double((long long)__hip_atomic_exchange(
+          reinterpret_cast<uint64_t*>(stage) + b * nchunks + i, (uint64_t)0, __ATOMIC_RELAXED,
+          __HIP_MEMORY_SCOPE_AGENT));   // read where it was written
+    all = reduce_block_sum(t);
+    if (threadIdx.x == 0) tickets[b] = 0u;
   }
-  __syncthreads();
-  if (ticket != (unsigned)(nchunks - 1)) return;
-  __threadfence();
-  double t = 0.0;
-  for (int i = threadIdx.x; i < nchunks; i += 256) t += __builtin_nontemporal_load(&stage[b * nchunks + i]);
-  const double all = block_tree_sum(t);
   if (threadIdx.x == 0) {
     const float L = (float)(all * scale);
     loss_out[b] = L;
     if (!__builtin_isfinite(L)) *flag = 1;
-    tickets[b] = 0u;
   }
 }
 
@@ -636,7 +655,7 @@ hipError_t launch_reduce_loss(const Layer& L, const double* part, double* stage,
                               float* loss_out, bool from_rows, double scale, hipStream_t s) {
   const int64_t per_batch = from_rows ? L.O * L.loss_cols : contract_partials_per_batch(L);
   const int nchunks = (int)((per_batch + kChunk - 1) / kChunk);
-  hipLaunchKernelGGL(k_reduce_loss, dim3((unsigned)nchunks, (unsigned)L.B), dim3(256), 0, s, part,
+  hipLaunchKernelGGL(k_reduce_loss, dim3((unsigned)nchunks, (unsigned)L.B), dim3(kReduceBlock), 0, s, part,
                      per_batch, nchunks, stage, tickets, scale, loss_out, L.flag);
   return hipGetLastError();
 }

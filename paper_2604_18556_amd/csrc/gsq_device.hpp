@@ -187,4 +187,36 @@ __device__ __forceinline__ uint16_t bf16_rne(float f) {
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// x shifted up by n lanes within each 16-lane row (lanes below the row start read 0).
+template <int kCtrl>
+__device__ __forceinline__ double dpp_shr(double x) {
+  const uint64_t b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, kCtrl, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), kCtrl, 0xF, 0xF, false);
+  return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+
+// x from lane 15 of the previous 16-lane row (kCtrl = row broadcast 15) or from lane 31
+// (row broadcast 31), added only in the rows of kRows; other lanes read 0.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ double dpp_bcast(double x) {
+  const uint64_t b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, kCtrl, kRows, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), kCtrl, kRows, 0xF, false);
+  return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+
+// Sum over the wavefront in a fixed order, left in lane 63: prefix sums within each 16-lane
+// row (shifts by 1, 2, 4, 8), then row 0's total into row 1 and row 2's into row 3, then the
+// first half's total into the second half.
+__device__ __forceinline__ double wave_sum_to_lane63(double x) {
+  x += dpp_shr<0x111>(x);
+  x += dpp_shr<0x112>(x);
+  x += dpp_shr<0x114>(x);
+  x += dpp_shr<0x118>(x);
+  x += dpp_bcast<0x142, 0xA>(x);
+  x += dpp_bcast<0x143, 0xC>(x);
+  return x;
+}
+
 }  // namespace gsq

@@ -266,3 +266,30 @@ def test_kept_memory_is_bounded_and_given_back(dev):
     assert kept > 0
     B.release_cached()
     assert free0 - torch.cuda.mem_get_info()[0] <= 64 << 20
+
+
+# ------------------------------------------------------------------ loss reduction
+# (batch, O, I): partials per layer below, at and past a chunk of 8192, several chunks, many layers
+@pytest.mark.parametrize("B_,O,I", [(1, 1, 16), (1, 8191, 16), (1, 8192, 16), (1, 8193, 16),
+                                    (3, 4100, 512), (70, 33, 272), (2, 30000, 256)])
+def test_loss_reduction(dev, B_, O, I):
+    """The step's loss against sum(-R G / 2) of the step's own R and G, several steps in a row (the
+    hand-over between chunks is used again each time), and the same bits from gsq_step_static."""
+    gen = torch.Generator(device=dev).manual_seed(O + I)
+    W = (torch.randn(B_, O, I, generator=gen, device=dev) * 0.02).to(torch.bfloat16)
+    X = torch.randn(B_, 64, I, generator=gen, device=dev)
+    H = torch.stack([x.t() @ x for x in X])
+    cfg = B.LayerConfig(O, I, _levels(4), 16, batch=B_, seed=4)
+    one, two = B.Layer(cfg, W, H), B.Layer(cfg, W, H)
+    R, G = torch.empty(B_, O, I, device=dev, dtype=torch.bfloat16), torch.empty(B_, O, I, device=dev)
+    for t in range(4):
+        prm = B.StepParams(tau=0.7, tau_next=0.7)
+        la, lb = torch.full((B_,), -1.0, device=dev), torch.full((B_,), -2.0, device=dev)
+        one.step(prm, loss_out=la)
+        one.intermediates(R, G)
+        two.step_static(prm, loss_out=lb)
+        assert torch.equal(la, lb)
+        want = (R.double() * G.double()).sum((1, 2)) * -0.5
+        # fp32 sums of four columns' terms per lane (2^-24 each, of either sign) and one rounding
+        size = (R.double() * G.double()).abs().sum((1, 2)) * 0.5
+        assert torch.all((la.double() - want).abs() <= 2.0 ** -22 * size), (t, la, want)
