@@ -188,7 +188,8 @@ __device__ __forceinline__ void slab_barrier() {
 // The instruction is written out because the builtin gives its result other registers than its
 // accumulator input once there are 64 of these, and moves them around.  What the compiler then
 // does not see is the time an accumulator takes to be readable by anything but another product:
-// acc_settled() waits for it, before the first product and after the last.
+// acc_settled() waits for it, before the first product and after the last.  The
+// operands come from LDS reads, whose waits the compiler sets; no vector instruction writes them.
 __device__ __forceinline__ void mfma_16x16x32(f32x4& acc, const bf16x8& h, const bf16x8& r) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(h), "v"(r));
 }
