@@ -1,5 +1,7 @@
 """The kernels that a call reaches only at certain sizes, alignments or options, at the sizes where
 each can go wrong: edges of tiles and blocks, remainders, the smallest and the largest of a range."""
+import gc
+
 import numpy as np
 import pytest
 
@@ -250,6 +252,8 @@ def test_layers_from_kept_memory(dev, prec):
 
 def test_kept_memory_is_bounded_and_given_back(dev):
     """Ended handles keep at most a sixteenth of the device's memory; release_cached frees it."""
+    gc.collect()   # what earlier tests left behind is not counted
+    torch.cuda.empty_cache()
     B.release_cached()
     torch.cuda.synchronize()
     free0, total = torch.cuda.mem_get_info()
