@@ -2,8 +2,8 @@
 //
 // A quantisation run makes and destroys one handle per layer.  A gigabyte from hipMalloc costs
 // several milliseconds, and tens where the driver has yet to clear memory freed just before: the
-// whole life of 4 experts of 2048 x 7168 in eight steps took 211 ms, of which 29 were kernels.
-// From kept blocks it takes 26 ms (with the present initialisation kernels).
+// whole life of 4 experts of 2048 x 7168 in eight steps took 34 to 211 ms, of which 29 were kernels.
+// From kept blocks it takes 24 ms (with the present kernels).
 //
 // What is kept is bounded (per device, kKeepShare of its memory and kBlocks blocks), goes back to
 // the device when an allocation of this library fails, when the device has less than kFreeShare
