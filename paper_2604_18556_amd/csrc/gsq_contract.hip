@@ -136,10 +136,12 @@ __device__ __forceinline__ bool pick_piece(const Plan& pl, int& b, int& tm, int&
 }
 
 // LDS layout of a slab: row r occupies 128 bytes as eight 16-byte chunks, chunk c stored at
-// position c ^ f(r), f(r) = (r ^ (r >> 3)) & 7.  The fragment reads (consecutive rows, one
-// chunk each) then fall on distinct banks for 8- and 16-lane access phases and for 32 or 64
-// banks.
-__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
+// position c ^ f(r), f(r) = (r / 2) & 7; two rows span the 64 banks.  A fragment read takes 16 rows,
+// chunk c in one 16 lanes and c ^ 1 in the next, and the hardware serves lanes 0-3, 12-15 and 20-27
+// together, then the others (measured: with f(r) = (r ^ (r / 8)) & 7, which is free of conflicts for
+// 16 consecutive lanes, every read took 4 cycles more).  With this f both sets, and consecutive lanes
+// too, fall on distinct banks.
+__device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 // Global->LDS copy of a wavefront's share of one operand slab: n instructions of eight rows, 16
 // bytes per lane.  `src` is wave-uniform (the slab's first column); off[j] is the lane's element
