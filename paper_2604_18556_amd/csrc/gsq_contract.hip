@@ -220,9 +220,9 @@ __device__ __forceinline__ void acc_settled(f32x4 (&acc)[MI][NJ]) {
 //
 // Bound by the power that the matrix cores may draw.  With random operands in registers, the
 // 16x16x32 form holds 2090 TFLOP/s on this chip and the 32x32x16 form 1824: half the accumulator
-// traffic per product lets the clock stay higher.  From 32x32x16 to 16x16x32 with the order below:
-// 4096 x 14336 1338 -> 1212 us (1.39 PFLOP/s), 8192 x 28672 10.1 -> 9.24 ms (1.46), 4096 x 4096
-// 132 -> 124 us, 16 x 2048 x 7168 2.66 -> 2.47 ms.
+// traffic per product lets the clock stay higher.  From 32x32x16 to 16x16x32 with the order below
+// and the swizzle above: 4096 x 14336 1338 -> 1132 us (1.49 PFLOP/s), 8192 x 28672 10.1 -> 8.60 ms
+// (1.57), 4096 x 4096 132 -> 121 us, 16 x 2048 x 7168 2.66 -> 2.29 ms.
 template <class P>
 __device__ __forceinline__ void contract_piece(const uint16_t* A, const uint16_t* Bt, float* Gp,
                                                const uint16_t* Rp, double* partial, int64_t Ipad,
@@ -266,7 +266,7 @@ __device__ __forceinline__ void contract_piece(const uint16_t* A, const uint16_t
   // The products of one half, and between them, one at a time, the fragment reads of the next half
   // and the slab loads: a load after every two reads.  The products have side effects for the
   // compiler, so this order stays.  Blocks are walked back and forth: one operand of each product
-  // is the last one's.  At 4096 x 14336: 1212 us so, 1270 with all reads before the loads, 1229 with
+  // is the last one's.  At 4096 x 14336 (before the present swizzle): 1212 us so, 1270 with all reads before the loads, 1229 with
   // the loads first, 1228 spread evenly over the half, 1351 one product apart instead of two; 1216
   // along R's blocks instead of H's.
   const auto half_slab = [&](const bf16x8 (&fa)[P::MI], const bf16x8 (&fb)[P::NJ], int n_loads,
@@ -385,10 +385,10 @@ __global__ __launch_bounds__(256, 1) void k_contract_bf16(const uint16_t* __rest
 // The plan of a layer's contraction on a GPU of num_cu compute units.  Tiles beyond a whole number
 // of rounds are cut where their pieces still fit one round: a piece per CU then takes about a half
 // or a third of a whole tile's time, against whole tiles on half the CUs or fewer.
-//   1024 x 4096 (64 tiles, as 256 quarters)              88 -> 45 us
-//   14336 x 4096 (3.5 rounds, the half as 256 halves)   448 -> 410 us
-//   4096 x 14336 (3.5 rounds)                          1376 us, the same as with the K range of
-//     the last tiles split over workgroups, which took a workspace and a second launch
+//   1024 x 4096 (64 tiles, as 256 quarters)              88 -> 45 us, 39 with the present MFMAs
+//   14336 x 4096 (3.5 rounds, the half as 256 halves)   448 -> 410 us, 340
+//   4096 x 14336 (3.5 rounds)                          1376 us, 1132, as with the K range of the
+//     last tiles split over workgroups, which took a workspace and a second launch
 // A quarter's K loop is bound by its loads: 32 KB per slab and CU at 64 B per clock take as long
 // as its MFMAs.
 //
