@@ -69,8 +69,9 @@ __global__ __launch_bounds__(kBlock) void k_forward_f64(ElemArgs a) {
   __shared__ __align__(16) float win[kMode == GSQ_RELAX_SHIFT ? GSQ_MAX_LEVELS * kWinRow : 4];
   if constexpr (kMode == GSQ_RELAX_SHIFT) fill_windows(win, a);
   const int cols = (a.I + kBlock - 1) / kBlock;   // blocks per row
-  const int64_t row = blockIdx.x / cols, col = (int64_t)(blockIdx.x % cols) * kBlock + threadIdx.x;
-  if (col >= a.I) return;
+  const int64_t row = (int64_t)blockIdx.y * a.rows_x + blockIdx.x / cols;
+  const int64_t col = (int64_t)(blockIdx.x % cols) * kBlock + threadIdx.x;
+  if (row >= a.rows || col >= a.I) return;
   const int64_t e = row * a.I + col;
   float l[K], cand[K], g[Z];
 #pragma unroll
@@ -95,7 +96,9 @@ __global__ __launch_bounds__(kBlock) void k_backward_f64(ElemArgs a) {
   __shared__ double part[2][kWaves];   // the wavefronts' sums: loss, scale gradient
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int cols = (a.I + kBlock - 1) / kBlock;   // blocks per row
-  const int64_t row = blockIdx.x / cols, col = (int64_t)(blockIdx.x % cols) * kBlock + threadIdx.x;
+  const int64_t row = (int64_t)blockIdx.y * a.rows_x + blockIdx.x / cols;
+  const int64_t col = (int64_t)(blockIdx.x % cols) * kBlock + threadIdx.x;
+  if (row >= a.rows) return;   // the whole workgroup
   const bool active = col < a.I;
   const double kt = (double)a.kappa * a.inv_tau_d;
   const double b1 = a.b1, b2 = a.b2, omb1 = 1.0 - b1, omb2 = 1.0 - b2;
@@ -164,7 +167,8 @@ __global__ __launch_bounds__(kBlock) void k_backward_f64(ElemArgs a) {
       if (!kLion) __builtin_nontemporal_store(v[k], a.V + o);
     }
   }
-  // sums over the wavefront, then over the workgroup
+  // sums over the wavefront, then over the workgroup, whose partial is that of its place in the grid
+  // (row cols + x % cols, but no division that is kept in registers until here)
   if (a.want_loss) {
     const double x = wave_sum_to_lane63(-0.5 * lsum);   // P = -G / 2
     if (lane == 63) part[0][wave] = x;
@@ -178,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_f64(ElemArgs a) {
     double x = part[0][0];
 #pragma unroll
     for (int i = 1; i < kWaves; ++i) x += part[0][i];
-    a.loss_part[blockIdx.x] = x;
+    a.loss_part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = x;
   }
   float s_new = s32;
   if constexpr (kScales) {
@@ -210,22 +214,25 @@ __global__ __launch_bounds__(kBlock) void k_backward_f64(ElemArgs a) {
   if (bad) *a.flag = 1;
 }
 
-// One block per row and 256 columns, in one dimension: with a loop over rows the compiler keeps the
-// polynomials' constants in scalar registers across it, more than there are, and reads them back
-// one lane at a time (385 such moves per row at 8 levels).
-dim3 lane_grid(const Layer& L) {
-  return dim3((unsigned)(L.B * L.O * ((L.I + kBlock - 1) / kBlock)));
+// One block per row and 256 columns: with a loop over rows the compiler keeps the polynomials'
+// constants in scalar registers across it, more than there are, and reads them back one lane at a
+// time (385 such moves per row at 8 levels).  Fills a.rows_x.
+dim3 lane_grid(const Layer& L, ElemArgs& a) {
+  const RowSplit sp = split_rows(L.B * L.O, (L.I + kBlock - 1) / kBlock);
+  a.rows_x = sp.rows_x;
+  return dim3(sp.gx, sp.gy);
 }
 
 template <int K, int kMode = GSQ_RELAX_GRID>
-hipError_t forward_k(const Layer& L, const ElemArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_forward_f64<K, kMode>), lane_grid(L), dim3(kBlock), 0, s, a);
+hipError_t forward_k(const Layer& L, ElemArgs a, hipStream_t s) {
+  const dim3 g = lane_grid(L, a);
+  hipLaunchKernelGGL((k_forward_f64<K, kMode>), g, dim3(kBlock), 0, s, a);
   return hipGetLastError();
 }
 
 template <int K, bool kMulti, int kMode, bool kLion>
-void backward_km(const Layer& L, const ElemArgs& a, bool sc, hipStream_t s) {
-  const dim3 g = lane_grid(L), b(kBlock);
+void backward_km(const Layer& L, ElemArgs a, bool sc, hipStream_t s) {
+  const dim3 g = lane_grid(L, a), b(kBlock);
   if (sc) hipLaunchKernelGGL((k_backward_f64<K, true, kMulti, kMode, kLion>), g, b, 0, s, a);
   else hipLaunchKernelGGL((k_backward_f64<K, false, kMulti, kMode, kLion>), g, b, 0, s, a);
 }

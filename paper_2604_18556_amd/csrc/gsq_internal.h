@@ -31,6 +31,7 @@ struct ElemArgs {
   int32_t want_loss;
   int64_t N;            // B*O*I
   int32_t rows;         // B*O
+  int32_t rows_x;       // fp64 kernels: rows per grid.y (split_rows)
   int32_t O, I, Opad, Ipad, gs, w_bf16;
   uint64_t seed;
   float c[GSQ_MAX_LEVELS];    // the grid
@@ -53,6 +54,20 @@ struct ElemArgs {
   float kappa_n, inv_tau_n;
   double inv_tau_n_d;
 };
+
+// The grid of a kernel that gives each row `cols` workgroups of 256 threads, in grid.x, without a
+// loop over rows.  A dimension of a launch holds fewer than 2^32 threads; with more, part of the work
+// is left out and no error reported.  So grid.x takes whole rows up to that and grid.y repeats it:
+// workgroup (x, y) has row y rows_x + x / cols, if there is one.
+struct RowSplit {
+  int32_t rows_x;
+  uint32_t gx, gy;
+};
+inline RowSplit split_rows(int64_t rows, int64_t cols) {
+  constexpr int64_t kMost = (int64_t{1} << 24) - 1;   // cols <= 2^16, as I <= 2^24
+  const int64_t fit = kMost / cols, rows_x = rows < fit ? rows : fit;
+  return {(int32_t)rows_x, (uint32_t)(rows_x * cols), (uint32_t)((rows + rows_x - 1) / rows_x)};
+}
 
 struct Layer;
 int64_t state_floats(const Layer& L);   // floats of one logit / moment array

@@ -213,6 +213,48 @@ def test_fp64_steps(dev, relax, K, gs, I, opt, samples, loss):
                            dlogits=inter["dlogits"])
 
 
+# A launch holds fewer than 2^32 threads in a dimension: 2^24 - 1 of these kernels' workgroups.
+def test_fp64_rows_beyond_one_grid_dimension(dev):
+    """17 million rows of one workgroup each, past what one grid dimension holds: two steps (the
+    second from the sample that the first drew) against the oracle on the rows at that edge and at
+    the ends of the first and last layer."""
+    B_, O, I, K = 5, 3_400_003, 16, 2
+    edge = (1 << 24) - 1 - 4 * O   # in the last layer
+    assert 0 < edge < O - 1
+    rows = np.array([0, 1, edge - 1, edge, edge + 1, O - 1])
+    print(f"[fp64 rows] {B_} x {O} x {I}", flush=True)
+    gen = torch.Generator(device=dev).manual_seed(1)
+    Wd = torch.randn(B_, O, I, generator=gen, device=dev) * 0.02
+    X = torch.randn(B_, 64, I, generator=gen, device=dev)
+    Hd = torch.stack([x.t() @ x for x in X])
+    layer = B.Layer(B.LayerConfig(O, I, _levels(K), 16, batch=B_, precision=B.PREC_FP32, seed=5), Wd, Hd)
+    # the oracle holds the sampled rows of the first and last layer, at their global noise indices
+    rcfg = ref.Config(O, I, _levels(K), 16, batch=B_, precision="fp32", seed=5)
+    W, Hs, sel = Wd.cpu().numpy(), ref.symmetrize(Hd.cpu().numpy())[[0, B_ - 1]], [0, B_ - 1]
+    st = ref.init_layer(rcfg, W, rows=rows, batches=sel)
+    big = torch.empty(B_, O, I, K, device=dev)
+    for t in range(2):
+        prm = B.StepParams(tau=0.6, tau_next=0.6, lr_scales=5e-5)
+        loss = torch.full((B_,), -1.0, device=dev)
+        layer.step(prm, loss_out=loss)
+        st, _, inter = ref.step(rcfg, W, Hs, st, oracle_params(prm), rows=rows, batches=sel, want=True)
+        got = {}
+        for n in ("logits", "m", "v", "scales", "m_s", "v_s"):
+            out = torch.empty(B_, O, 1, device=dev) if n in ("scales", "m_s", "v_s") else big
+            tt = layer.get_state(**{n: out})
+            got[n] = out[sel][:, rows].cpu().numpy()
+        assert_state_close(ref.State(*got.values(), tt), st, inter["G"], 1e-6, t + 1,
+                           label=f"step {t}", dlogits=inter["dlogits"])
+        R, G = torch.empty(B_, O, I, device=dev), torch.empty(B_, O, I, device=dev)
+        layer.intermediates(R, G)
+        for b in range(B_):   # one partial per row, every one of them summed
+            terms = R[b].double() * G[b].double() * -0.5
+            assert abs(loss[b].double() - terms.sum()) <= 2.0 ** -23 * terms.abs().sum()
+    layer.check()
+    layer.destroy()
+    B.release_cached()
+
+
 # ------------------------------------------------------------------ memory kept between handles
 @pytest.mark.parametrize("prec", ["bf16", "fp32"])
 def test_layers_from_kept_memory(dev, prec):
