@@ -272,12 +272,15 @@ gsq_status gsq_check(gsq_layer* h, hipStream_t stream);
 
 /*
  * End a handle (NULL-safe; synchronises the device).  Its buffers are freed, or kept for the next
- * handle on the same device while they come to at most 1/16 of the device's memory and 1/8 of it is
- * free; what is kept is freed when an allocation of this library needs the room.
+ * handles on the same device, at most 1/16 of the device's memory in all.  What is kept is freed
+ * when an allocation of this library needs the room, and when a handle ends while less than 1/8 of
+ * the device is free (then nothing of that handle is kept either).  Other allocators of the process
+ * do not see it: a caller that needs the device's last 1/16 for them calls gsq_release_cached.
  */
 gsq_status gsq_layer_destroy(gsq_layer* h);
 
-/* Free the buffers kept from ended handles, on every device. */
+/* Free the buffers kept from ended handles, on every device.  Due before hipDeviceReset, which would
+ * take them away unseen. */
 gsq_status gsq_release_cached(void);
 
 /* Message of the last error on this thread ("" if none). */

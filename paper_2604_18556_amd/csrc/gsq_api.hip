@@ -100,8 +100,12 @@ void free_layer(gsq::Layer* L, bool idle) {
     (void)hipEventDestroy(p.second.second);
   }
   for (hipEvent_t e : L->event_pool) (void)hipEventDestroy(e);
-  const size_t limit = idle ? gsq::DevicePool::limit() : 0;
-  for (int i = 0; i < L->n_bufs; ++i) g_pool.give(L->device, L->bufs[i].p, L->bufs[i].bytes, limit);
+  if (idle) {
+    const size_t limit = gsq::DevicePool::limit();
+    for (int i = 0; i < L->n_bufs; ++i) g_pool.give(L->device, L->bufs[i].p, L->bufs[i].bytes, limit);
+  } else {
+    for (int i = 0; i < L->n_bufs; ++i) (void)hipFree(L->bufs[i].p);
+  }
   if (L->flag) (void)hipFree(L->flag);
   delete L;
 }

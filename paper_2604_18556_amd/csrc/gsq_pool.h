@@ -5,10 +5,11 @@
 // whole life of 4 experts of 2048 x 7168 in eight steps took 34 to 211 ms, of which 29 were kernels.
 // From kept blocks it takes 24 ms (with the present kernels).
 //
-// What is kept is bounded (per device, kKeepShare of its memory and kBlocks blocks), goes back to
-// the device when an allocation of this library fails, when the device has less than kFreeShare
-// left free, or by gsq_release_cached(), and is handed out whole, to one handle at a time.  A block
-// comes back only after the device is idle, so its next user may be on any stream or thread.
+// What is kept is bounded (per device, a kKeepShare-th of its memory and kBlocks blocks) and is handed
+// out whole, to one handle at a time.  All of it goes back to the device when a handle ends while
+// less than a kFreeShare-th of the device is free (kept blocks and the handle's own count as used),
+// when an allocation of this library fails, or by gsq_release_cached().  A block comes here only
+// after the device is idle, so its next user may be on any stream or thread.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -49,20 +50,22 @@ class DevicePool {
     return e;
   }
 
-  // Keep a block nothing on the device uses any more, or free it.
+  // Keep a block nothing on the device uses any more, or free it, and as many of the device's older
+  // ones as bring what is kept there to `limit`.
   void give(int dev, void* p, size_t bytes, size_t limit) {
     std::lock_guard<std::mutex> lock(mu_);
-    if (bytes > limit) {
-      (void)hipFree(p);
-      return;
-    }
-    size_t kept = bytes;
+    const bool keep = bytes <= limit;
+    size_t kept = keep ? bytes : 0;
     for (int i = 0; i < n_; ++i) kept += b_[i].dev == dev ? b_[i].bytes : 0;
     for (int i = 0; i < n_ && kept > limit;) {   // the oldest first
       if (b_[i].dev != dev) { ++i; continue; }
       kept -= b_[i].bytes;
       (void)hipFree(b_[i].p);
       remove(i);
+    }
+    if (!keep) {
+      (void)hipFree(p);
+      return;
     }
     if (n_ == kBlocks) {
       (void)hipFree(b_[0].p);
@@ -84,7 +87,7 @@ class DevicePool {
     return any;
   }
 
-  // Bytes that may be kept on the current device now.
+  // Bytes that may be kept on the current device now: none while too little of it is free.
   static size_t limit() {
     size_t free_bytes = 0, total = 0;
     if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {

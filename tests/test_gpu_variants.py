@@ -314,6 +314,26 @@ def test_kept_memory_is_bounded_and_given_back(dev):
     assert free0 - torch.cuda.mem_get_info()[0] <= 64 << 20
 
 
+def test_kept_memory_goes_back_when_little_is_free(dev):
+    """A handle that ends while less than an eighth of the device is free gives back its own memory and
+    what earlier ones left: another allocator of the process holds the rest."""
+    gc.collect()
+    torch.cuda.empty_cache()
+    B.release_cached()
+    W = torch.zeros(1, 8192, 256, device=dev, dtype=torch.bfloat16)
+    H = torch.eye(256, device=dev).reshape(1, 256, 256)
+    free0, total = torch.cuda.mem_get_info()
+    one, two = (B.Layer(B.LayerConfig(8192, 256, _levels(8), 128), W, H) for _ in range(2))
+    one.destroy()
+    free1 = torch.cuda.mem_get_info()[0]
+    other = torch.empty(free1 - total // 10, device=dev, dtype=torch.uint8)
+    print(f"[kept memory] {torch.cuda.mem_get_info()[0] >> 20} MiB free", flush=True)
+    two.destroy()
+    del other
+    torch.cuda.empty_cache()
+    assert free0 - torch.cuda.mem_get_info()[0] <= 64 << 20
+
+
 # ------------------------------------------------------------------ loss reduction
 # (batch, O, I): partials per layer below, at and past a chunk of 8192, several chunks, many layers
 @pytest.mark.parametrize("B_,O,I", [(1, 1, 16), (1, 8191, 16), (1, 8192, 16), (1, 8193, 16),

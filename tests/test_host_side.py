@@ -1,5 +1,6 @@
 """Host code of the library that no call reaches without a GPU, compiled on its own with the host
-compiler: the split of a launch over the grid's dimensions."""
+compiler: the split of a launch over the grid's dimensions, and what is kept of ended handles' device
+memory (with a device of the test's own in place of HIP's)."""
 import os
 import subprocess
 
@@ -8,16 +9,19 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def _run(tmp_path, source, *args):
-    """Output lines of a C++ program that sees the library's headers and links nothing of HIP."""
-    src, exe = tmp_path / "prog.cpp", tmp_path / "prog"
+def _compile(folder, source):
+    """A C++ program that sees the library's headers and links nothing of HIP."""
+    src, exe = folder / "prog.cpp", folder / "prog"
     src.write_text(source)
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     "-I", os.path.join(ROOT, "include"),
                     "-I", os.path.join(ROOT, "paper_2604_18556_amd", "csrc"), str(src), "-o", str(exe)],
                    check=True, capture_output=True, text=True)
-    r = subprocess.run([str(exe), *args], check=True, capture_output=True, text=True)
-    return r.stdout.splitlines()
+    return str(exe)
+
+
+def _lines(exe, *args):
+    return subprocess.run([exe, *args], check=True, capture_output=True, text=True).stdout.splitlines()
 
 
 SPLIT = r"""
@@ -40,10 +44,98 @@ def test_rows_split_over_the_grid(tmp_path):
     cases = [(1, 1), (7, 3), (EDGE, 1), (EDGE + 1, 1), (1 << 24, 2), (17_000_015, 1), (1 << 30, 1),
              (EDGE // 2, 2), (EDGE // 2 + 1, 2), (5, EDGE // 5), (6, EDGE // 5), (70_000, 256),
              (1, 65536), (255, 65536), (256, 65536), (2000, 65536)]
-    lines = _run(tmp_path, SPLIT, *(str(x) for c in cases for x in c))
+    lines = _lines(_compile(tmp_path, SPLIT), *(str(x) for c in cases for x in c))
     assert len(lines) == len(cases)
     for (rows, cols), line in zip(cases, lines):
         rows_x, gx, gy = map(int, line.split())
         assert gx == rows_x * cols and 0 < gx <= EDGE, (rows, cols, line)
         assert (gy - 1) * rows_x < rows <= gy * rows_x and 0 < gy <= 65535, (rows, cols, line)
         assert gy == 1 or (rows_x + 1) * cols > EDGE, (rows, cols, line)
+
+
+# A device of 1600 bytes, of which a sixteenth (100) may be kept and an eighth (200) must be free.
+POOL = r"""
+#include "gsq_pool.h"
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <string>
+static std::map<void*, size_t> live;
+static size_t total = 1600, others = 0;
+static size_t in_use() {
+  size_t n = others;
+  for (auto& b : live) n += b.second;
+  return n;
+}
+extern "C" hipError_t hipMalloc(void** p, size_t n) {
+  if (in_use() + n > total) return hipErrorOutOfMemory;
+  live[*p = std::malloc(n)] = n;
+  return hipSuccess;
+}
+extern "C" hipError_t hipFree(void* p) {
+  if (!live.erase(p)) std::puts("freed twice");
+  return hipSuccess;   // the address is not used again: each stays told apart
+}
+extern "C" hipError_t hipMemGetInfo(size_t* f, size_t* t) {
+  *t = total;
+  *f = total - in_use();
+  return hipSuccess;
+}
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+
+// words: a<dev>:<bytes> take a block, g give the oldest one held back, o<bytes> what others use, r<dev> release
+int main(int argc, char** argv) {
+  static gsq::DevicePool pool;
+  struct Held { int dev; void* p; size_t n; };
+  std::map<int, Held> held;
+  int first = 0, next = 0;
+  for (int i = 1; i < argc; ++i) {
+    const char* w = argv[i] + 1;
+    if (argv[i][0] == 'a') {
+      Held h{std::atoi(w), nullptr, 0};
+      const size_t n = std::atoi(std::string(w).substr(std::string(w).find(':') + 1).c_str());
+      if (pool.take(h.dev, n, &h.p, &h.n) == hipSuccess) held[next++] = h; else std::printf("none ");
+    } else if (argv[i][0] == 'g') {
+      const Held h = held[first];
+      held.erase(first++);
+      pool.give(h.dev, h.p, h.n, gsq::DevicePool::limit());
+    } else if (argv[i][0] == 'o') {
+      others = std::atoi(w);
+    } else {
+      pool.release(std::atoi(w));
+    }
+    size_t kept = in_use() - others;
+    for (auto& h : held) kept -= h.second.n;
+    std::printf("%zu ", kept);
+  }
+  std::puts("");
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def pool(tmp_path_factory):
+    return _compile(tmp_path_factory.mktemp("pool"), POOL)
+
+
+@pytest.mark.parametrize("words,kept", [
+    # kept, and taken again where at most a quarter is wasted
+    ("a0:40 g a0:40 g a0:33 g a0:31", "0 40 0 40 0 40 40"),
+    # never more than a sixteenth: the oldest goes, a block above it is not kept
+    ("a0:40 a0:50 a0:30 g g g", "0 0 0 40 90 80"),
+    ("a0:40 a0:101 g g", "0 0 40 40"),
+    # an eighth must be free (the ended handle's own block not counted): else all of the device's goes
+    ("a0:40 a0:20 g o1400 g", "0 0 40 40 0"),
+    ("a0:40 a0:101 g o1400 g", "0 0 40 40 0"),
+    ("a0:40 a0:20 g o1341 g", "0 0 40 40 0"),
+    ("a0:40 a0:20 g o1340 g", "0 0 40 40 60"),
+    # another device's blocks are not this one's
+    ("a1:40 a0:30 a0:20 g g o1400 g", "0 0 0 40 70 70 40"),
+    # an allocation that does not fit takes what is kept on its device, once
+    ("a0:40 g o1500 a0:90 a0:90", "0 40 40 0 none 0"),
+    ("a0:40 a1:30 g g r0 r-1", "0 0 40 70 30 0"),
+])
+def test_kept_memory_policy(pool, words, kept):
+    """Bytes kept after each word of the program above."""
+    line, = _lines(pool, *words.split())
+    assert line.split() == kept.split()
