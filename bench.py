@@ -23,7 +23,6 @@ and with two noise draws per step.
     python bench.py --copy-calibration   # plain device copy of known size, for PMC scaling
 """
 import argparse
-import hashlib
 import json
 import os
 import sys
@@ -31,6 +30,8 @@ import time
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
+
+from paper_2604_18556_amd.rocprof_summary import source_digest  # noqa: E402  (loads nothing)
 
 METRIC = "GSQ steps/sec per layer (fwd+bwd+update) + % HBM / MFMA peak, 1 MI355X"
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
@@ -82,13 +83,9 @@ def harden_bytes(w, hard_loss):
     return n * per + n // gs * 8
 
 
-def source_sha(path):
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
-
-
 def measured_traffic(kernel, workload):
-    """HBM bytes per launch from the committed PMC summary, if it matches the current source."""
+    """HBM bytes per launch from the committed PMC summary, if it matches the current source and
+    the headers it includes."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
@@ -99,7 +96,7 @@ def measured_traffic(kernel, workload):
     if not rec:
         return None
     src = os.path.join(ROOT, "paper_2604_18556_amd", "csrc", rec["source"])
-    if not os.path.exists(src) or source_sha(src) != rec["source_sha256"]:
+    if not os.path.exists(src) or source_digest(rec["source"]) != rec["source_sha256"]:
         return None
     return rec["bytes_per_launch"]
 
@@ -236,7 +233,10 @@ def kernel_table(kern, work, w, steps):
     return per_kernel
 
 
-KERNEL_SOURCE = {"forward": "gsq_elem.hip", "backward": "gsq_elem.hip", "contract": "gsq_contract.hip"}
+def kernel_source(kernel, w):
+    if kernel == "contract":
+        return "gsq_contract.hip"
+    return "gsq_elem.hip" if w.precision == "bf16" else "gsq_elem64.hip"
 
 
 def dominant_roofline(per_kernel, w, profiled=True):
@@ -249,7 +249,7 @@ def dominant_roofline(per_kernel, w, profiled=True):
     return {"bound": d["bound"], "achieved": d["achieved"], "peak": d["peak"], "unit": d["unit"],
             "frac": d["frac"], "traffic": measured_traffic(dom, w.name) if profiled else None,
             "kernel": dom,
-            "avg_ms": d["avg_ms"], "source": KERNEL_SOURCE[dom]}
+            "avg_ms": d["avg_ms"], "source": kernel_source(dom, w)}
 
 
 def make_config(B, w):

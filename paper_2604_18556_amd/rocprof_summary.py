@@ -10,8 +10,8 @@
 FETCH_SIZE and WRITE_SIZE are in KiB per dispatch.  ``traffic`` scales each by the ratio of
 the known byte count of a plain device copy (bench.py --copy-calibration) to what the same
 counter reports for that copy, and records the HBM bytes per launch of one GSQ kernel,
-together with the SHA-256 of the kernel's source file, into a JSON file that bench.py reads
-(it reports the traffic only while the source is unchanged).
+together with the SHA-256 of the kernel's source file and the headers it includes, into a JSON
+file that bench.py reads (it reports the traffic only while these are unchanged).
 
 ``mfma`` reads one counter pass holding SQ_VALU_MFMA_BUSY_CYCLES, SQ_INSTS_VALU_MFMA_MOPS_BF16 and
 GRBM_GUI_ACTIVE, and gives for the contraction: the clock while the GPU is active
@@ -26,16 +26,38 @@ import csv
 import hashlib
 import json
 import os
+import re
 import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-KERNEL_MATCH = {  # short name -> (substring of the mangled / demangled kernel name, source file)
+SOURCE_DIRS = (os.path.join(PKG, "csrc"), os.path.join(os.path.dirname(PKG), "include"))
+# short name -> (substring of the mangled / demangled kernel name, source file); the first that fits
+KERNEL_MATCH = {
+    "forward_f64": ("k_forward_f64", "gsq_elem64.hip"),
+    "backward_f64": ("k_backward_f64", "gsq_elem64.hip"),
     "forward": ("k_forward", "gsq_elem.hip"),
     "backward": ("k_backward", "gsq_elem.hip"),
     "contract": ("k_contract_bf16", "gsq_contract.hip"),
     "contract_f32": ("k_contract_f32", "gsq_contract.hip"),
     "harden": ("k_harden", "gsq_elem.hip"),
 }
+
+
+def source_digest(src, dirs=SOURCE_DIRS):
+    """SHA-256 over a source file and the headers in ``dirs`` that it includes with quotes, at any
+    depth, each once: all of this library's text that its kernels are compiled from."""
+    h, todo, seen = hashlib.sha256(), [src], set()
+    while todo:
+        name = todo.pop(0)
+        if name in seen:
+            continue
+        seen.add(name)
+        path = next(p for p in (os.path.join(d, name) for d in dirs) if os.path.exists(p))
+        with open(path, "rb") as f:
+            text = f.read()
+        h.update(name.encode() + b"\0" + text)
+        todo += [m.decode() for m in re.findall(rb'^\s*#\s*include\s+"([^"]+)"', text, re.M)]
+    return h.hexdigest()
 
 
 def short(name):
@@ -145,14 +167,14 @@ def cmd_traffic(a):
     fk = f[(a.kernel, "FETCH_SIZE")][0] * sf * 1024
     wk = w[(a.kernel, "WRITE_SIZE")][0] * sw * 1024
     src = KERNEL_MATCH[a.kernel][1]
-    sha = hashlib.sha256(open(os.path.join(PKG, "csrc", src), "rb").read()).hexdigest()
+    sha = source_digest(src)
     print(f"# HBM traffic of one {a.kernel} launch of the optimisation steps, workload {a.workload}"
           f"\n# command: {a.cmd}\n")
     print(f"copy calibration: {a.copy_bytes} bytes read and written; FETCH_SIZE scale {sf:.4f}, "
           f"WRITE_SIZE scale {sw:.4f}")
     print(f"{a.kernel}: FETCH_SIZE {f[(a.kernel, 'FETCH_SIZE')][0]:.1f} KiB/dispatch -> {fk / 1e6:.2f} MB")
     print(f"{a.kernel}: WRITE_SIZE {w[(a.kernel, 'WRITE_SIZE')][0]:.1f} KiB/dispatch -> {wk / 1e6:.2f} MB")
-    print(f"{a.kernel}: traffic {(fk + wk) / 1e6:.2f} MB per launch; source {src} sha256 {sha[:16]}...")
+    print(f"{a.kernel}: traffic {(fk + wk) / 1e6:.2f} MB per launch; source {src} and its headers sha256 {sha[:16]}...")
     if a.json:
         data = json.load(open(a.json)) if os.path.exists(a.json) else {}
         data[f"{a.kernel}:{a.workload}"] = {"bytes_per_launch": fk + wk, "fetch_bytes": fk,

@@ -5,6 +5,7 @@ harden) count; the MFMA summary turns GRBM_GUI_ACTIVE, SQ_VALU_MFMA_BUSY_CYCLES 
 SQ_INSTS_VALU_MFMA_MOPS_BF16 into the clock, the busy share and the bf16 rate."""
 import csv
 import json
+import shutil
 
 import pytest
 
@@ -58,6 +59,35 @@ def test_traffic_scales_by_the_copy_and_counts_only_the_steps(tmp_path, capsys):
     assert rec["bytes_per_launch"] == pytest.approx((4000 + 1000) * 1024)
     assert rec["source"] == "gsq_elem.hip" and len(rec["source_sha256"]) == 64
     assert "traffic" in capsys.readouterr().out
+
+
+def test_a_changed_header_invalidates_the_traffic_record(tmp_path):
+    """The digest that a record carries covers the headers its kernel's source includes, and theirs:
+    an edit of any of them changes it, one of another file of the library does not."""
+    dirs = []
+    for d in rs.SOURCE_DIRS:
+        dirs.append(tmp_path / d.rsplit("/", 1)[1])
+        shutil.copytree(d, dirs[-1])
+    names = {"gsq_elem.hip": {"gsq_elem.hip", "gsq_elem.hpp", "gsq_device.hpp", "gsq_internal.h", "gsq.h"},
+             "gsq_elem64.hip": {"gsq_elem64.hip", "gsq_elem.hpp", "gsq_device.hpp", "gsq_internal.h", "gsq.h"},
+             "gsq_contract.hip": {"gsq_contract.hip", "gsq_device.hpp", "gsq_internal.h", "gsq.h"}}
+    assert set(names) == {src for _, src in rs.KERNEL_MATCH.values()}
+    files = [p for d in dirs for p in sorted(d.iterdir())]
+    before = {src: rs.source_digest(src, dirs) for src in names}
+    assert before == {src: rs.source_digest(src) for src in names}
+    for path in files:
+        text = path.read_text()
+        path.write_text(text + "\n")
+        changed = {src for src in names if rs.source_digest(src, dirs) != before[src]}
+        assert changed == {src for src in names if path.name in names[src]}, path.name
+        path.write_text(text)
+
+
+def test_the_fp64_kernels_are_told_apart():
+    """The FP32 precision's kernels have names and a source file of their own."""
+    f64 = "void gsq::(anonymous namespace)::k_backward_f64<4, true, false, 0, false>(gsq::ElemArgs)"
+    assert rs.short(f64) == "backward_f64" and rs.KERNEL_MATCH["backward_f64"][1] == "gsq_elem64.hip"
+    assert rs.short(BW) == "backward" and rs.KERNEL_MATCH["backward"][1] == "gsq_elem.hip"
 
 
 def test_mfma_summary_clock_busy_share_and_rate(tmp_path, capsys):
