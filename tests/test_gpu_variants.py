@@ -213,6 +213,45 @@ def test_fp64_steps(dev, relax, K, gs, I, opt, samples, loss):
                            dlogits=inter["dlogits"])
 
 
+# groups inside a wavefront, one wavefront, and across two and four
+@pytest.mark.parametrize("gs", [16, 64, 128, 256])
+@pytest.mark.parametrize("opt", [B.OPT_ADAM, B.OPT_LION])
+@pytest.mark.parametrize("where,value", [("W", np.inf), ("W", np.nan), ("H", np.nan), ("H", -np.inf)])
+def test_fp64_steps_with_values_that_are_not_finite(dev, gs, opt, where, value):
+    """One weight or one diagonal element of H that is not finite makes a row or a column of G so.  A
+    step without a loss sets the flag; each array of the state is finite just where the oracle's is
+    and agrees there, so that the groups and wavefronts beside it are untouched.  Lion's step is a
+    sign, which is 0 for NaN here and NaN in the oracle: its logits and scales stay finite."""
+    W, H = layer_inputs(5, 512, batch=2, bf16=False, seed=gs)
+    rcfg = ref.Config(5, 512, _levels(4), gs, batch=2, precision="fp32", seed=5)
+    st = ref.init_layer(rcfg, W)
+    if where == "W":
+        W[1, 2, 300] = value
+    else:
+        H[1, 300, 300] = value
+    pair = Pair(rcfg, W, H, dev)
+    pair.put(st)
+    prm = B.StepParams(tau=0.6, tau_next=0.6, lr_scales=5e-5, optimizer=opt)
+    pair.step(prm, want_loss=False)
+    with np.errstate(all="ignore"):
+        st, _ = ref.step(rcfg, W, pair.Hs, st, oracle_params(prm))
+    ls, ss = pair.shapes()
+    got = {n: torch.empty(ls, device=dev) for n in ("logits", "m", "v")}
+    got.update({n: torch.empty(ss, device=dev) for n in ("scales", "m_s", "v_s")})
+    with pytest.raises(B.GsqError) as e:   # the state comes with the flag's report
+        pair.layer.get_state(**got)
+    assert e.value.status == B.GSQ_ENONFINITE
+    for n in got:
+        x, y = got[n].cpu().numpy(), getattr(st, n)
+        fin = np.isfinite(y)
+        assert fin[0].all() and fin[1].any() and not (n in ("m", "m_s") and fin[1].all()), n
+        want = np.ones_like(fin) if opt == B.OPT_LION and n in ("logits", "scales") else fin
+        np.testing.assert_array_equal(np.isfinite(x), want, err_msg=n)
+        # m, v: 2^-24 of their size and the rounding of G; logits, scales: a step's size whatever the
+        # gradient's, so the same of the step, next to which 1e-5 of the largest logit is wide
+        assert np.abs(x[fin] - y[fin]).max() <= 1e-5 * np.abs(y[fin]).max(), n
+
+
 # A launch holds fewer than 2^32 threads in a dimension: 2^24 - 1 of these kernels' workgroups.
 def test_fp64_rows_beyond_one_grid_dimension(dev):
     """17 million rows of one workgroup each, past what one grid dimension holds: two steps (the
