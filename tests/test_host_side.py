@@ -1,7 +1,9 @@
 """Host code of the library that no call reaches without a GPU, compiled on its own with the host
 compiler: the split of a launch over the grid's dimensions, and what is kept of ended handles' device
-memory (with a device of the test's own in place of HIP's)."""
+memory (with a device of the test's own in place of HIP's); and what the compiler makes of kernels that
+no result shows."""
 import os
+import re
 import subprocess
 
 import pytest
@@ -139,3 +141,28 @@ def test_kept_memory_policy(pool, words, kept):
     """Bytes kept after each word of the program above."""
     line, = _lines(pool, *words.split())
     assert line.split() == kept.split()
+
+
+def test_fp64_kernels_keep_their_values_in_registers(tmp_path):
+    """The LDS and scratch of the fp64 kernels as compiled for gfx950: the local shift's window table
+    (512 bytes) and eight wavefront sums (64) at most, so that no array of a thread's own has been put
+    into either."""
+    from paper_2604_18556_amd import build
+    try:
+        cc = build.hipcc()
+    except RuntimeError as e:
+        pytest.skip(str(e))
+    r = subprocess.run([cc, *build.FLAGS, "--offload-device-only", "-Rpass-analysis=kernel-resource-usage",
+                        "-c", os.path.join(build.CSRC, "gsq_elem64.hip"), "-o", str(tmp_path / "x.o")],
+                       check=True, capture_output=True, text=True)
+    used = {}
+    for line in r.stderr.splitlines():
+        m = re.search(r"(Function Name|ScratchSize|LDS Size)[^:]*: (\S+)", line)
+        if m and m[1] == "Function Name":
+            used[m[2]] = name = {}
+        elif m:
+            name[m[1]] = int(m[2])
+    used = {n: u for n, u in used.items() if "ward_f64" in n}
+    assert len(used) == 9 + 9 * 8   # seven grids, shift, ternary; scales, samples, optimiser
+    for n, u in used.items():
+        assert u["ScratchSize"] == 0 and u["LDS Size"] <= 512 + 64, (n, u)
