@@ -70,21 +70,27 @@ __device__ __forceinline__ float load_w(const ElemArgs& a, int64_t e) {
                   : static_cast<const float*>(a.W)[e];
 }
 
+// Row of the workgroup, of which there are `cols` per row (split_rows); past the last one: none.  The
+// rows and those of a further grid.y fit 31 bits: in 64 the backward takes 1 % more.
+__device__ __forceinline__ int lane_row(const ElemArgs& a, int cols) {
+  return (int)(blockIdx.y * (uint32_t)a.rows_x + blockIdx.x / (uint32_t)cols);
+}
+
 template <int K, int kMode>
 __global__ __launch_bounds__(kBlock) void k_forward_f64(ElemArgs a) {
   constexpr int Z = noise_count<K, kMode>();
   __shared__ __align__(16) float win[kMode == GSQ_RELAX_SHIFT ? GSQ_MAX_LEVELS * kWinRow : 4];
   if constexpr (kMode == GSQ_RELAX_SHIFT) fill_windows(win, a);
   const int cols = (a.I + kBlock - 1) / kBlock;   // blocks per row
-  const int64_t row = (int64_t)blockIdx.y * a.rows_x + blockIdx.x / cols;
+  const int row = lane_row(a, cols);
   const int64_t col = (int64_t)(blockIdx.x % cols) * kBlock + threadIdx.x;
   if (row >= a.rows || col >= a.I) return;
-  const int64_t e = row * a.I + col;
+  const int64_t e = (int64_t)row * a.I + col;
   float l[K], cand[K], g[Z];
 #pragma unroll
   for (int k = 0; k < K; ++k) l[k] = a.L[state_off(e, k, K)];
   const float w = load_w(a, e);
-  const double s = (double)a.S[row * (a.I / a.gs) + col / a.gs];
+  const double s = (double)a.S[(int64_t)row * (a.I / a.gs) + col / a.gs];
   const uint32_t j0 = kMode == GSQ_RELAX_SHIFT ? a.J0[e] : 0u;
   coord_candidates<K, kMode>(cand, a, win, j0, 0);
   lane_noise<Z, kMode>(g, a, (uint64_t)e, a.t, (uint32_t)a.sample);
@@ -103,7 +109,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_f64(ElemArgs a) {
   __shared__ double part[2][kWaves];   // the wavefronts' sums: loss, scale gradient
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int cols = (a.I + kBlock - 1) / kBlock;   // blocks per row
-  const int64_t row = (int64_t)blockIdx.y * a.rows_x + blockIdx.x / cols;
+  const int row = lane_row(a, cols);
   const int64_t col = (int64_t)(blockIdx.x % cols) * kBlock + threadIdx.x;
   if (row >= a.rows) return;   // the whole workgroup
   const bool active = col < a.I;
@@ -114,8 +120,8 @@ __global__ __launch_bounds__(kBlock) void k_backward_f64(ElemArgs a) {
   const int in_wave = min(a.gs, 64);
   const bool wide = kScales && a.gs > 64;   // a group spans gs / 64 wavefronts
   bool bad = false;
-  const int64_t e = row * a.I + (active ? col : 0);
-  const int64_t sidx = row * gpr + (active ? col / a.gs : 0);
+  const int64_t e = (int64_t)row * a.I + (active ? col : 0);
+  const int64_t sidx = (int64_t)row * gpr + (active ? col / a.gs : 0);
   const int64_t gidx = active ? padded_index(a, row, col) : 0;
   const float s32 = a.S[sidx];
   const double s = s32;
