@@ -36,7 +36,7 @@ from paper_2604_18556_amd.rocprof_summary import source_digest  # noqa: E402  (l
 METRIC = "GSQ steps/sec per layer (fwd+bwd+update) + % HBM / MFMA peak, 1 MI355X"
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 PEAK_BF16_TFLOPS = 2500.0      # dense bf16 MFMA
-PEAK_FP64_TFLOPS = 78.6        # fp64 vector (the FP32 precision accumulates in fp64)
+PEAK_FP64_TFLOPS = 78.6        # fp64, matrix cores (the FP32 precision accumulates in fp64)
 DEFAULT_WORKLOAD = "moe-64x2048x7168-superblock"
 TARGET_LAYER = "mlp-down-4096x14336-k8"   # the layer the matrix-core target names
 VARIANT_OF = {"moe-64x2048x7168-superblock": "moe-64x2048x7168-superblock-shift8"}
@@ -227,8 +227,8 @@ def kernel_table(kern, work, w, steps):
         elif name == "contract":
             tf = work[name][1] / (avg * 1e-3) / 1e12
             peak = PEAK_BF16_TFLOPS if w.precision == "bf16" else PEAK_FP64_TFLOPS
-            entry.update(bound="mfma" if w.precision == "bf16" else "alu", achieved=tf, peak=peak,
-                         unit="TFLOP/s", frac=tf / peak, flops_per_launch=work[name][1])
+            entry.update(bound="mfma", achieved=tf, peak=peak, unit="TFLOP/s", frac=tf / peak,
+                         flops_per_launch=work[name][1])
         per_kernel[name] = entry
     return per_kernel
 

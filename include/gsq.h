@@ -163,7 +163,7 @@ gsq_status gsq_step(gsq_layer* h, const gsq_step_params* p, float* loss_out, hip
  * buffers are never grown.
  * Limits (GSQ_EINVAL before anything is enqueued): samples at most the most any earlier gsq_step
  * on this handle used (1 for a new handle); with loss_out, batch * O * ceil(I / 256) <= 4194304
- * row partials, batch * ceil(O * ceil(I / 256) / 2048) <= 65536 chunk sums and batch <= 65536.
+ * row partials, batch * ceil(O * ceil(I / 256) / 8192) <= 65536 chunk sums and batch <= 65536.
  * The handle's device must be current.  Every call on one GPU shares that GPU's scratch, which
  * keeps the last call's contents: calls that overlap on one GPU (other streams, threads or
  * handles) race, and the caller must order them.

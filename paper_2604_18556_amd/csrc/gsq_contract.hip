@@ -5,7 +5,8 @@
 // BF16 precision: R and H in bf16, products accumulated in fp32 on the matrix cores
 // (v_mfma 16x16x32 bf16).  Because H is symmetric, column i of H is row i, so both operands
 // are read along their contiguous dimension.
-// FP32 precision: fp32 operands, fp64 accumulation on the vector units.
+// FP32 precision: fp32 operands, fp64 accumulation on the fp64 matrix cores
+// (v_mfma 16x16x4 f64).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -221,8 +222,8 @@ __device__ __forceinline__ void acc_settled(f32x4 (&acc)[MI][NJ]) {
 // Bound by the power that the matrix cores may draw.  With random operands in registers, the
 // 16x16x32 form holds 2090 TFLOP/s on this chip and the 32x32x16 form 1824: half the accumulator
 // traffic per product lets the clock stay higher.  From 32x32x16 to 16x16x32 with the order below
-// and the swizzle above: 4096 x 14336 1338 -> 1132 us (1.49 PFLOP/s), 8192 x 28672 10.1 -> 8.60 ms
-// (1.57), 4096 x 4096 132 -> 121 us, 16 x 2048 x 7168 2.66 -> 2.29 ms.
+// and the swizzle above (one box): 4096 x 14336 1318 -> 1152 us (1.46 PFLOP/s), 8192 x 28672
+// 10.0 -> 8.69 ms (1.55), 4096 x 4096 134 -> 118 us, 16 x 2048 x 7168 2.67 -> 2.33 ms.
 template <class P>
 __device__ __forceinline__ void contract_piece(const uint16_t* A, const uint16_t* Bt, float* Gp,
                                                const uint16_t* Rp, double* partial, int64_t Ipad,
@@ -266,9 +267,9 @@ __device__ __forceinline__ void contract_piece(const uint16_t* A, const uint16_t
   // The products of one half, and between them, one at a time, the fragment reads of the next half
   // and the slab loads: a load after every two reads.  The products have side effects for the
   // compiler, so this order stays.  Blocks are walked back and forth: one operand of each product
-  // is the last one's.  At 4096 x 14336 (before the present swizzle): 1212 us so, 1270 with all reads before the loads, 1229 with
-  // the loads first, 1228 spread evenly over the half, 1351 one product apart instead of two; 1216
-  // along R's blocks instead of H's.
+  // is the last one's.  At 4096 x 14336, with a swizzle that cost each read four cycles: 1212 us so,
+  // 1270 with all reads before the loads, 1229 with the loads first, 1228 spread evenly over the
+  // half, 1351 one product apart instead of two; 1216 along R's blocks instead of H's.
   const auto half_slab = [&](const bf16x8 (&fa)[P::MI], const bf16x8 (&fb)[P::NJ], int n_loads,
                              auto&& next_read, auto&& next_load) {
     constexpr int kLoads = P::A_LOADS > P::B_LOADS ? P::A_LOADS : P::B_LOADS;
@@ -385,15 +386,22 @@ __global__ __launch_bounds__(256, 1) void k_contract_bf16(const uint16_t* __rest
 // The plan of a layer's contraction on a GPU of num_cu compute units.  Tiles beyond a whole number
 // of rounds are cut where their pieces still fit one round: a piece per CU then takes about a half
 // or a third of a whole tile's time, against whole tiles on half the CUs or fewer.
-//   1024 x 4096 (64 tiles, as 256 quarters)              88 -> 45 us, 39 with the present MFMAs
-//   14336 x 4096 (3.5 rounds, the half as 256 halves)   448 -> 410 us, 340
-//   4096 x 14336 (3.5 rounds)                          1376 us, 1132, as with the K range of the
+//   1024 x 4096 (64 tiles, as 256 quarters)              88 -> 45 us, 37 with the present MFMAs
+//   14336 x 4096 (3.5 rounds, the half as 256 halves)   448 -> 410 us, 349
+//   4096 x 14336 (3.5 rounds)                          1376 us, 1152, as with the K range of the
 //     last tiles split over workgroups, which took a workspace and a second launch
 // A quarter's K loop is bound by its loads: 32 KB per slab and CU at 64 B per clock take as long
 // as its MFMAs.
 //
-// Blocks pay where a layer's block fills an XCD's 32 CUs about, and there are enough for each
-// XCD; else the tiles of all layers are numbered through.
+// Blocks are taken where a layer's block about fills an XCD's 32 CUs and there is one for each XCD;
+// else the tiles of all layers are numbered through.  Contraction, us, with blocks | without:
+//   fewer than 24 tiles in a block: 8 x 256 x 1024 28.8 | 14.0, 16 x 512 x 1024 31.9 | 22.4,
+//     32 x 1024 x 1280 130 | 119, 8 x 768 x 1792 46.0 | 45.9, 64 x 512 x 1024 72.5 | 74.5
+//   fewer than 8 blocks: 3 x 2048 x 2048 56.0 | 50.2, 6 x 2048 x 1024 35.1 | 34.1
+//   else: 3 x 4096 x 4096 286 | 311, 16 x 2048 x 7168 2280 | 2360, 64 x 768 x 2048 350 | 358, level at
+//     4 x 2048 x 2048 and 12 x 2048 x 1008
+// The line is not the best one everywhere: 64 x 1408 x 2048 817 | 661, 60 x 2048 x 1408 656 | 507,
+// 8 x 1536 x 4096 378 | 308, 16 x 768 x 2048 104 | 92, 2 x 2048 x 7168 322 | 303.
 Plan make_plan(const Layer& L) {
   Plan pl{};
   pl.tiles_m = (int)(L.Opad / BM);
@@ -533,8 +541,8 @@ int f32_tile(const Layer& L) {
 // stage[b * nchunks + c], and the last block of layer b to finish (a ticket counter, reset by that
 // block) sums the chunks in order.  Bound by latency: wavefront sums in registers and one exchange
 // through LDS instead of a tree of eight barriers, chunks of 8192 instead of 2048, so that up to
-// 8192 partials need no hand-over, and a hand-over without a fence.  256 x 256: 4.1 -> 1.9 us,
-// 1024 x 4096: 6.0 -> 5.3 (8.2 with the fence), 4096 x 4096: 7.2 -> 5.3.
+// 8192 partials need no hand-over, and a hand-over without a fence (below, with what it rests on).
+// 256 x 256: 4.1 -> 1.9 us, 1024 x 4096: 6.0 -> 5.3 (8.2 with the fence), 4096 x 4096: 7.2 -> 5.3.
 constexpr int kPer = 8;                 // partials per thread, all loaded before summing
 constexpr int kReduceBlock = 1024;
 constexpr int kChunk = kReduceBlock * kPer;
@@ -577,6 +585,11 @@ __global__ __launch_bounds__(kReduceBlock) void k_reduce_loss(const double* part
       // The chunk sum goes to where every XCD sees it, and the ticket is drawn once that has
       // answered: both are device-wide read-modify-writes, and the second needs the first's result.
       // A fence instead would write back the XCD's whole L2, full of the backward's output.
+      // This rests on the hardware, not on the language's memory model, which orders relaxed
+      // operations on two addresses by no dependence: gfx950 performs a device-scope
+      // read-modify-write where all XCDs meet and returns its old value from there, so the sum is in
+      // place before the ticket's request leaves the wavefront; and the reader's exchanges of the
+      // sums leave only after the last ticket has returned (the barrier and the branch below).
       const uint64_t old = __hip_atomic_exchange(reinterpret_cast<uint64_t*>(stage) + b * nchunks + c,
                                                  (uint64_t)__double_as_longlong(all),
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

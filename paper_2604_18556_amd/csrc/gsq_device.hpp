@@ -52,8 +52,10 @@ __device__ __forceinline__ float uniform01(uint32_t x) {
 }
 
 // fp64 functions for the arguments met here, to about 1 ulp of fp64: the library's, which also serve
-// every other argument, take 98, 42 and 22 vector instructions, these 26, 20 and 12.  Polynomials
-// by interpolation at Chebyshev points.
+// every other argument, take 98, 42 and 22 vector instructions, these 26, 20 and 12.  The reductions
+// are those of Cody and Waite, "Software Manual for the Elementary Functions" (1980): ln through
+// (m - 1) / (m + 1), exp through a multiple of ln 2 in two words; the root is Goldschmidt's coupled
+// iteration (1964).  Polynomials by interpolation at Chebyshev points, with coefficients of our own.
 
 // ln x of a positive normal x: x = 2^e m with m in [sqrt(1/2), sqrt(2)), f = m - 1,
 // s = f / (2 + f), ln m = f - s (f - z P(z)) with z = s^2 and 2 atanh(s) = 2 s + s z P(z); the

@@ -6,8 +6,8 @@
 // layer had few wavefronts, each with four coordinates' chains one after the other.  The state's
 // accesses of 256 bytes per wavefront are wide enough for it.  A workgroup owns 256 columns of a
 // row, so a scale group lies inside it; what crosses its wavefronts goes through LDS in a fixed
-// order.  With the short fp64 functions, 1024 x 2048, K = 8: backward 366 -> 224 us, forward
-// 127 -> 67; 256 x 256, K = 4: 23 -> 8.3 us.
+// order.  With the short fp64 functions, 1024 x 2048, K = 8: backward 332 -> 206 us, forward
+// 109 -> 57; 256 x 256, K = 4: backward 24.5 -> 9.8 us.
 #include <hip/hip_runtime.h>
 
 #include "gsq_elem.hpp"

@@ -128,8 +128,8 @@ def cmd_mfma(a):
     first_harden = min((d for d, (k, _) in meta.items() if k == "harden"), default=float("inf"))
     groups = collections.defaultdict(list)
     for d, (k, t) in sorted(meta.items()):
-        if k == "contract" or "k_contract_fixup" in k:
-            groups[(k if k == "contract" else "fixup", "step" if d < first_harden else "hard loss")].append(d)
+        if k == "contract":
+            groups[(k, "step" if d < first_harden else "hard loss")].append(d)
     print(f"# rocprofv3 MFMA counters of the contraction, median over dispatches\n# command: {a.cmd}\n"
           f"# GPU: {n_xcc} XCCs, {n_simd} SIMDs; peak {PEAK_BF16_TFLOPS:.0f} TFLOP/s bf16 at "
           f"{NOMINAL_GHZ} GHz\n")
@@ -137,9 +137,6 @@ def cmd_mfma(a):
           f"{'GFLOP':>9} {'TFLOP/s':>8} {'frac':>6} {'frac@clock':>10} {'lds_conflict':>12}")
     for (k, kind), ds in sorted(groups.items()):
         us = median([meta[d][1] * 1e6 for d in ds])
-        if k == "fixup":
-            print(f"{k:<10} {kind:<10} {len(ds):>3} {us:>9.1f}")
-            continue
         ghz = median([per[d]["GRBM_GUI_ACTIVE"] / n_xcc / meta[d][1] / 1e9 for d in ds])
         busy = median([per[d]["SQ_VALU_MFMA_BUSY_CYCLES"] / (per[d]["GRBM_GUI_ACTIVE"] / n_xcc * n_simd)
                        for d in ds])
