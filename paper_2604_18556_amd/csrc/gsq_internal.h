@@ -31,8 +31,8 @@ struct ElemArgs {
   int32_t want_loss;
   int64_t N;            // B*O*I
   int32_t rows;         // B*O
-  int32_t rows_x;       // fp64 kernels: rows per grid.y (split_rows)
   int32_t O, I, Opad, Ipad, gs, w_bf16;
+  int32_t rows_x;       // fp64 kernels: rows per grid.y (split_rows)
   uint64_t seed;
   float c[GSQ_MAX_LEVELS];    // the grid
   int32_t n_grid;
