@@ -127,9 +127,9 @@ bool alloc(gsq::Layer& L, T** p, size_t bytes) {
 
 // One from the runtime itself.
 template <typename T>
-bool alloc_new(T** p, size_t bytes) {
+bool alloc_new(const gsq::Layer& L, T** p, size_t bytes) {
   void* q = nullptr;
-  if (hipMalloc(&q, bytes) != hipSuccess) {
+  if (g_pool.take_new(L.device, bytes, &q) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
@@ -295,7 +295,7 @@ gsq_status gsq_layer_init(const gsq_config* cfg, const void* W, int32_t w_dtype,
   }
   // the flag comes from the runtime on every call, so that what refuses an allocation (a stream
   // capture) refuses a handle too, whatever is kept
-  bool ok = alloc_new(&L.flag, sizeof(int)) &&
+  bool ok = alloc_new(L, &L.flag, sizeof(int)) &&
             alloc(L, &L.W, L.N * (L.w_bf16 ? 2 : 4)) &&
             alloc(L, &L.H, (size_t)(L.B * L.Ipad * L.Ipad) * relem) &&
             alloc(L, &L.L, gsq::state_floats(L) * 4) && alloc(L, &L.M, gsq::state_floats(L) * 4) &&
@@ -357,8 +357,7 @@ gsq_status gsq_layer_init(const gsq_config* cfg, const void* W, int32_t w_dtype,
 static gsq_status grow_sample_slots(gsq::Layer& L, int M) {
   const size_t npad = (size_t)(L.B * L.Opad * L.Ipad), bytes = (size_t)M * npad * 4;
   float* G = nullptr;
-  if (!alloc_new(&G, bytes) && !(g_pool.release(L.device) && alloc_new(&G, bytes)))
-    return fail(GSQ_ENOMEM, "no room for %d samples", M);
+  if (!alloc_new(L, &G, bytes)) return fail(GSQ_ENOMEM, "no room for %d samples", M);
   const hipError_t e = hipDeviceSynchronize();   // no launch on any stream still reads the old one
   if (e != hipSuccess) {
     (void)hipFree(G);

@@ -42,6 +42,12 @@ class DevicePool {
       }
     }
     *got = bytes;
+    return take_new(dev, bytes, p);
+  }
+
+  // A block from the runtime itself.  What is kept makes room for it, but stays where the runtime
+  // refuses for another reason (a stream capture).
+  hipError_t take_new(int dev, size_t bytes, void** p) {
     hipError_t e = hipMalloc(p, bytes);
     if (e == hipErrorOutOfMemory && release(dev)) {
       (void)hipGetLastError();

@@ -64,12 +64,14 @@ POOL = r"""
 #include <string>
 static std::map<void*, size_t> live;
 static size_t total = 1600, others = 0;
+static bool refuse = false;
 static size_t in_use() {
   size_t n = others;
   for (auto& b : live) n += b.second;
   return n;
 }
 extern "C" hipError_t hipMalloc(void** p, size_t n) {
+  if (refuse) return hipErrorStreamCaptureUnsupported;
   if (in_use() + n > total) return hipErrorOutOfMemory;
   live[*p = std::malloc(n)] = n;
   return hipSuccess;
@@ -85,7 +87,8 @@ extern "C" hipError_t hipMemGetInfo(size_t* f, size_t* t) {
 }
 extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 
-// words: a<dev>:<bytes> take a block, g give the oldest one held back, o<bytes> what others use, r<dev> release
+// words: a<dev>:<bytes> take a block, n<dev>:<bytes> a new one, g give the oldest one held back,
+// o<bytes> what others use, c<0|1> refuse allocations as in a stream capture, r<dev> release
 int main(int argc, char** argv) {
   static gsq::DevicePool pool;
   struct Held { int dev; void* p; size_t n; };
@@ -93,16 +96,20 @@ int main(int argc, char** argv) {
   int first = 0, next = 0;
   for (int i = 1; i < argc; ++i) {
     const char* w = argv[i] + 1;
-    if (argv[i][0] == 'a') {
+    if (argv[i][0] == 'a' || argv[i][0] == 'n') {
       Held h{std::atoi(w), nullptr, 0};
       const size_t n = std::atoi(std::string(w).substr(std::string(w).find(':') + 1).c_str());
-      if (pool.take(h.dev, n, &h.p, &h.n) == hipSuccess) held[next++] = h; else std::printf("none ");
+      const hipError_t e = argv[i][0] == 'a' ? pool.take(h.dev, n, &h.p, &h.n)
+                                             : pool.take_new(h.dev, h.n = n, &h.p);
+      if (e == hipSuccess) held[next++] = h; else std::printf("none ");
     } else if (argv[i][0] == 'g') {
       const Held h = held[first];
       held.erase(first++);
       pool.give(h.dev, h.p, h.n, gsq::DevicePool::limit());
     } else if (argv[i][0] == 'o') {
       others = std::atoi(w);
+    } else if (argv[i][0] == 'c') {
+      refuse = *w == '1';
     } else {
       pool.release(std::atoi(w));
     }
@@ -136,11 +143,21 @@ def pool(tmp_path_factory):
     # an allocation that does not fit takes what is kept on its device, once
     ("a0:40 g o1500 a0:90 a0:90", "0 40 40 0 none 0"),
     ("a0:40 a1:30 g g r0 r-1", "0 0 40 70 30 0"),
+    # nor does a new one, and one that is refused for another reason leaves it
+    ("a0:40 g n0:20 n0:20 g", "0 40 40 40 60"),
+    ("a0:40 g o1599 n0:1 o1560 n0:4", "0 40 40 0 0 0"),
+    ("a0:40 g c1 n0:4 a0:90 a0:40 c0 n0:4", "0 40 40 none 40 none 40 0 0 0"),
 ])
 def test_kept_memory_policy(pool, words, kept):
     """Bytes kept after each word of the program above."""
     line, = _lines(pool, *words.split())
     assert line.split() == kept.split()
+
+
+def test_every_allocation_is_one_that_kept_memory_makes_room_for():
+    csrc = os.path.join(ROOT, "paper_2604_18556_amd", "csrc")
+    assert [n for n in sorted(os.listdir(csrc)) if "hipMalloc(" in open(os.path.join(csrc, n)).read()] \
+        == ["gsq_pool.h"]
 
 
 def test_fp64_kernels_keep_their_values_in_registers(tmp_path):
